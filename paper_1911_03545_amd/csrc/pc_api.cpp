@@ -984,7 +984,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         (want_ravg && (st2 = ensure(c, B_RHIST, sizeof(double) * nout))) ||
         (want_ravg && (st2 = ensure(c, B_OUTR, sizeof(double) * nout))) ||
         (st2 = ensure(c, B_WSQ, (wfixed ? 24 : 8) * (size_t)ncat)) ||
-        (st2 = ensure(c, B_CTRS, sizeof(int32_t) * PC_STREAMS * PC_STREAM_STRIDE)))
+        (st2 = ensure(c, B_CTRS, PC_STREAM_BYTES)))
         return st2;
     {
         void *zp[PC_ZERO_MAX];
@@ -993,7 +993,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         zp[nz] = c->buf[B_ICNT].p;
         zb[nz++] = sizeof(int32_t) * (size_t)maxblocks;
         zp[nz] = c->buf[B_CTRS].p;
-        zb[nz++] = sizeof(int32_t) * PC_STREAMS * PC_STREAM_STRIDE;
+        zb[nz++] = PC_STREAM_BYTES;
         zp[nz] = c->buf[B_HIST].p;
         zb[nz++] = sizeof(unsigned long long) * nout;
         if (weighted) {

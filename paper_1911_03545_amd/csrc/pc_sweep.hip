@@ -1071,28 +1071,47 @@ __device__ __forceinline__ int tri_end(int j0, int j1, int iend)
 // following streams once it is exhausted.  Stream s owns the contiguous
 // items [s n / S, (s + 1) n / S), so a wave's consecutive items are
 // neighbours (same catalogue, nearby cells).  Returns n_items when every
-// stream is exhausted.  On a stream that last gave the wave an item, lane 0
-// increments the counter at once (one round trip per item; the one increment
-// past the end is harmless, as every take compares with the length).  On the
-// streams it moves on to (`probe`), it reads the counter first and only
-// increments it while items remain, so exhausted streams cost one load each.
+// stream is exhausted.  Lane 0 increments the stream's counter at once (one
+// round trip per item; increments past the end are harmless, as every take
+// compares with the length).  The take that first finds a stream empty sets
+// its bit in a mask beside the counters, so a wave that moves on (`probe`)
+// reads one word to know the streams that may still hold items, instead of
+// one counter after the other (64 round trips after a wave's last item).
+static_assert(PC_STREAMS == 64, "one bit per stream");
 __device__ __forceinline__ int wave_fetch(int *ctrs, int n_items, int lane, int &s, bool &probe)
 {
-    for (int tries = 0; tries < PC_STREAMS; tries++) {
+    unsigned long long *done =
+        reinterpret_cast<unsigned long long *>(ctrs + PC_STREAMS * PC_STREAM_STRIDE);
+    unsigned long long empty = 0;   // streams known to be exhausted
+    for (int tries = 0; tries <= PC_STREAMS; tries++) {
+        if (probe) {
+            const unsigned long long m =
+                __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            empty |= 1ull << s;
+            empty |= (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)m) |
+                     (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(m >> 32))
+                         << 32;
+            if (!~empty)
+                return n_items;
+            // the first open stream after s, in circular order
+            const int r = (s + 1) & (PC_STREAMS - 1);
+            const unsigned long long open = ~empty;
+            const unsigned long long rot = r ? (open >> r) | (open << (PC_STREAMS - r)) : open;
+            s = (r + __ffsll((long long)rot) - 1) & (PC_STREAMS - 1);
+        }
         const int first = (int)(((long long)n_items * s) / PC_STREAMS);
         const int len = (int)(((long long)n_items * (s + 1)) / PC_STREAMS) - first;
-        int v = len;
+        int v = 0;
         if (lane == 0) {
-            int *c = ctrs + s * PC_STREAM_STRIDE;
-            if (!probe || __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < len)
-                v = atomicAdd(c, 1);
+            v = atomicAdd(ctrs + s * PC_STREAM_STRIDE, 1);
+            if (v == len)
+                atomicOr(done, 1ull << s);
         }
         v = __builtin_amdgcn_readfirstlane(v);
         if (v < len) {
             probe = false;
             return first + v;
         }
-        s = (s + 1) & (PC_STREAMS - 1);
         probe = true;
     }
     return n_items;
@@ -1319,7 +1338,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             if (v < len) {
                 next = first + v;
             } else {
-                stream = (stream + 1) & (PC_STREAMS - 1);
+                if (v == len && lane == 0)
+                    atomicOr(reinterpret_cast<unsigned long long *>(
+                                 a.counter + PC_STREAMS * PC_STREAM_STRIDE),
+                             1ull << stream);
                 probe = true;
                 next = wave_fetch(a.counter, n_items, lane, stream, probe);
             }
