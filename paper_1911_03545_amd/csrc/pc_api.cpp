@@ -1273,10 +1273,16 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         }
     }
     per_cu = std::max(per_cu, 1);
-    int nwg = (ctl.capture || async_items)
-                  ? c->num_cu * per_cu
-                  : (int)std::min<int64_t>((n_items + waves - 1) / waves,
-                                           (int64_t)c->num_cu * per_cu);
+    // one wave per work item up to the resident workgroups.  Where the count
+    // stays on the device the last one, with a quarter of headroom, sizes the
+    // launch (the waves take items until none are left, so it need not be
+    // exact): every workgroup copies the table and merges a histogram, which
+    // a full grid paid for 1024 workgroups also when 230 had work
+    const int64_t want_items = (ctl.capture || async_items)
+                                   ? (int64_t)c->last_items + c->last_items / 4
+                                   : (int64_t)n_items;
+    int nwg = (int)std::min<int64_t>((want_items + waves - 1) / waves,
+                                     (int64_t)c->num_cu * per_cu);
     nwg = std::max(nwg, 1);
     c->stats.sweep_workgroups = nwg;
     c->stats.hist_copies = copies;

@@ -671,7 +671,9 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
     L.phi = off; off = align8(off + sizeof(float) * nq);
     L.q = off;   off = align8(off + sizeof(double) * nq);
     const size_t esz = wide ? sizeof(uint16_t) : sizeof(uint8_t);
-    L.tbl = off; off = align8(off + esz * tbl_n);
+    // (the sweep copies the table in 16-byte pieces)
+    off = (off + 15) & ~(size_t)15;
+    L.tbl = off; off = (off + esz * tbl_n + 15) & ~(size_t)15;
     L.total = off;
 
     out->hdr = h;

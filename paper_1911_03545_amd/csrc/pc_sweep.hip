@@ -1216,15 +1216,15 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     LDS unsigned char *sm = (LDS unsigned char *)smem;
     {
         const int tid = threadIdx.x;
-        if (T16) {
-            LDS uint16_t *tbl = (LDS uint16_t *)(LDS unsigned char *)s_tbl;
-            const uint16_t *src = (const uint16_t *)a.tbl;
-            for (int k = tid; k < a.B.tbl_n; k += kSweepThreads)
-                tbl[k] = src[k];
-        } else {
-            LDS unsigned char *tbl = (LDS unsigned char *)s_tbl;
-            const unsigned char *src = (const unsigned char *)a.tbl;
-            for (int k = tid; k < a.B.tbl_n; k += kSweepThreads)
+        // the table in 16-byte pieces (byte by byte this copy took 64 round
+        // trips of every thread at the start of every workgroup); the planner
+        // aligns the table and pads its end to 16 bytes
+        {
+            typedef unsigned v4u __attribute__((ext_vector_type(4)));
+            LDS v4u *tbl = (LDS v4u *)(LDS unsigned char *)s_tbl;
+            const v4u *src = (const v4u *)a.tbl;
+            const int n16 = (a.B.tbl_n * (T16 ? 2 : 1) + 15) / 16;
+            for (int k = tid; k < n16; k += kSweepThreads)
                 tbl[k] = src[k];
         }
         // float bands: the r / rp edges, then (rppi) the pi edges
