@@ -36,7 +36,7 @@ enum BufId {
     B_CNT, B_START1, B_START2, B_CELLOF, B_RANKOF, B_PERM, B_REC, B_WOFF, B_LAY, B_COLS,
     B_X1, B_Y1, B_Z1, B_XD1, B_YD1, B_ZD1, B_WD1, B_CS1,
     B_X2, B_Y2, B_Z2, B_XD2, B_YD2, B_ZD2, B_WD2, B_CS2, B_Q1, B_Q2,
-    B_SCANTMP, B_BCNT, B_BOFF, B_BLOCKS, B_ICNT, B_IOFF, B_ITEMS, B_ICELL,
+    B_SCANTMP, B_BLOCKS, B_ICNT, B_IOFF, B_ITEMS, B_ICELL,
     B_BINS, B_BANDS, B_MISC, B_HIST, B_WHIST, B_OUTC, B_OUTW, B_RHIST, B_OUTR, B_PART, B_CTRS, B_CATS1, B_CATS2, B_UV1, B_UV2, B_WSQ,
     B_COUNT
 };
@@ -46,8 +46,9 @@ enum {
     M_FLAGS = 0,        // unsigned
     M_RQCOUNT = 16,     // unsigned
     M_CAND = 32,        // u64
-    M_SIZES = 40,       // 2 int32: work items, blocks (copied by the finalize kernel)
+    M_SIZES = 40,       // 2 int32: work items, blocks
     M_FLUSH = 48,       // unsigned: mid-sweep histogram flushes
+    M_COUNTED = 52,     // int32: work items counted ahead of the list (first calls)
     M_OUT6 = 64,        // 6 doubles
     M_WFIX = 128,       // pc_wfixed: grid of the fixed-point weight sums
     M_SIZE = 256
@@ -674,10 +675,11 @@ cf_status stage_side(cf_ctx *c, const cf_catalog *d, int ncat, bool radec, bool 
 // catalogue k are k * ncell .. (k + 1) * ncell - 1, so the sorted arrays hold
 // the catalogues one after the other, each in cell order.
 // Q (or B_COUNT: none): (x, y, z, |b|^2) in float32 of every sorted point,
-// side by side, for sweeps that expand x and y (with Z; X and Y not written)
+// side by side, for sweeps that expand x and y (with Z; X and Y not written).
+// blocks (or NULL): receives the side's blocks of up to 64 points.
 cf_status grid_side(cf_ctx *c, const SideData &s, const pc_cat *cats_dev, bool weighted,
                     const pc_grid &g, BufId start, BufId X, BufId Y, BufId Z, BufId XD, BufId YD,
-                    BufId ZD, BufId WD, BufId CS, BufId Q, unsigned *flags)
+                    BufId ZD, BufId WD, BufId CS, BufId Q, unsigned *flags, pc_block *blocks)
 {
     const int64_t n = s.ntot;
     const int64_t ncells = (int64_t)s.ncat * g.ncell;
@@ -730,7 +732,7 @@ cf_status grid_side(cf_ctx *c, const SideData &s, const pc_cat *cats_dev, bool w
                                 dptr<int32_t>(c, CS), dptr<float>(c, X), dptr<float>(c, Y),
                                 dptr<float>(c, Z), dptr<double>(c, XD), dptr<double>(c, YD),
                                 dptr<double>(c, ZD), weighted ? dptr<double>(c, WD) : nullptr,
-                                qd, flags));
+                                qd, flags, blocks));
         return CF_OK;
     }
     HIPCHK(pc::launch_zero(c->stream, c->buf[B_CNT].p, sizeof(int32_t) * (size_t)ncells));
@@ -746,6 +748,9 @@ cf_status grid_side(cf_ctx *c, const SideData &s, const pc_cat *cats_dev, bool w
                               dptr<double>(c, XD), dptr<double>(c, YD), dptr<double>(c, ZD),
                               weighted ? dptr<double>(c, WD) : nullptr, qd,
                               dptr<int32_t>(c, CS)));
+    if (blocks)
+        HIPCHK(pc::launch_block_emit(c->stream, s.ncat * ncolc, nz, dptr<int32_t>(c, start),
+                                     blocks));
     return CF_OK;
 }
 
@@ -1121,16 +1126,22 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // ---- work-list and sweep buffers, cleared by one kernel ahead of the
     // gridding (the host issues it while nothing else waits on it) ----------
     const int32_t ncol = g.n[0] * g.n[1] * ncat;   // columns of every catalogue
-    const int64_t maxblocks = n1 / PC_BLOCK_I + ncol + 1;
+    const int64_t nblocks = n1 / PC_BLOCK_I + ncol;   // places of the block array
+    const int64_t item_wgs = pc::item_workgroups(nblocks, g, autocorr ? 1 : 0);
+    // The work list in block order, or (small single catalogues) in the order
+    // in which its workgroups finish, which saves the counting pass and the
+    // scan.  Block order keeps a wave's successive items on the same j points:
+    // without it the sweep is 2% slower on 10^6 points and 9% on 1.5*10^5 by
+    // 6*10^5 cross points (437 -> 475 us, for 6 us saved here), but no slower
+    // up to 10^5, where the list takes 15 us in place of 24.  (Batched calls
+    // meet their catalogues one after the other.)
+    const bool ordered = priv || n1 + (autocorr ? 0 : n2) > 131072;
     const int chunk = opt.chunk > 0 ? std::min(opt.chunk, 1 << 20) : 2048;
-    if ((st2 = ensure(c, B_BCNT, sizeof(int32_t) * (size_t)ncol)) ||
-        (st2 = ensure(c, B_BOFF, sizeof(int32_t) * (size_t)(ncol + 1))) ||
-        (st2 = ensure(c, B_BLOCKS, sizeof(pc_block) * (size_t)maxblocks)) ||
-        (st2 = ensure(c, B_ICNT, sizeof(int32_t) * (size_t)maxblocks)) ||
-        (st2 = ensure(c, B_IOFF, sizeof(int32_t) * (size_t)(maxblocks + 1))) ||
+    if ((st2 = ensure(c, B_BLOCKS, sizeof(pc_block) * (size_t)nblocks)) ||
+        (ordered && (st2 = ensure(c, B_ICNT, sizeof(int32_t) * (size_t)item_wgs))) ||
+        (ordered && (st2 = ensure(c, B_IOFF, sizeof(int32_t) * (size_t)(item_wgs + 1)))) ||
         (st2 = ensure(c, B_SCANTMP, sizeof(int32_t) * pc::scan_tmp_elems(std::max<int64_t>(
-                                        std::max<int64_t>(maxblocks, ncol),
-                                        (int64_t)ncat * g.ncell)))) ||
+                                        item_wgs, (int64_t)ncat * g.ncell)))) ||
         (st2 = ensure(c, B_HIST, sizeof(unsigned long long) * nout)) ||
         (st2 = ensure(c, B_WHIST, (wfixed ? 24 : 8) * nout)) ||
         (st2 = ensure(c, B_OUTC, sizeof(unsigned long long) * nout)) ||
@@ -1144,8 +1155,6 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         void *zp[PC_ZERO_MAX];
         size_t zb[PC_ZERO_MAX];
         int nz = 0;
-        zp[nz] = c->buf[B_ICNT].p;
-        zb[nz++] = sizeof(int32_t) * (size_t)maxblocks;
         zp[nz] = c->buf[B_CTRS].p;
         zb[nz++] = PC_STREAM_BYTES;
         zp[nz] = c->buf[B_HIST].p;
@@ -1165,11 +1174,12 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // (|b|^2 for the expanded form: on the j side only)
     if ((st2 = grid_side(c, s1, cats1_dev, weighted, g, B_START1, B_X1, B_Y1, B_Z1, B_XD1, B_YD1,
                          B_ZD1, B_WD1, B_CS1, (xy_mag > 0.0 && autocorr) ? B_Q1 : B_COUNT,
-                         flags)))
+                         flags, dptr<pc_block>(c, B_BLOCKS))))
         return st2;
     if (!autocorr &&
         (st2 = grid_side(c, s2, cats2_dev, weighted, g, B_START2, B_X2, B_Y2, B_Z2, B_XD2,
-                         B_YD2, B_ZD2, B_WD2, B_CS2, xy_mag > 0.0 ? B_Q2 : B_COUNT, flags)))
+                         B_YD2, B_ZD2, B_WD2, B_CS2, xy_mag > 0.0 ? B_Q2 : B_COUNT, flags,
+                         nullptr)))
         return st2;
     // fixed-point weight sums: the grid 2^Q of this call's pair weights
     pc::pc_wfixed *wfx = wfixed ? (pc::pc_wfixed *)(misc(c) + M_WFIX) : nullptr;
@@ -1215,18 +1225,24 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // ---- work list ---------------------------------------------------------
     const int32_t *start1 = dptr<int32_t>(c, B_START1);
     const int32_t *start2 = autocorr ? start1 : dptr<int32_t>(c, B_START2);
-    HIPCHK(pc::launch_block_count(c->stream, ncol, g.n[2], start1, dptr<int32_t>(c, B_BCNT)));
-    HIPCHK(pc::scan_exclusive(c->stream, dptr<int32_t>(c, B_BCNT), ncol, dptr<int32_t>(c, B_BOFF),
-                              dptr<int32_t>(c, B_SCANTMP)));
-    HIPCHK(pc::launch_block_emit(c->stream, ncol, g.n[2], start1, dptr<int32_t>(c, B_BOFF),
-                                 dptr<pc_block>(c, B_BLOCKS)));
-    const int32_t *nblocks_dev = dptr<int32_t>(c, B_BOFF) + ncol;
+    const pc_block *blocks = dptr<pc_block>(c, B_BLOCKS);
     unsigned long long *cand = (unsigned long long *)(misc(c) + M_CAND);
-    HIPCHK(pc::launch_item_count(c->stream, (int32_t)maxblocks, nblocks_dev,
-                                 dptr<pc_block>(c, B_BLOCKS), g, start2, dptr<int32_t>(c, B_CS1),
-                                 autocorr ? 1 : 0, chunk, dptr<int32_t>(c, B_ICNT), cand));
-    HIPCHK(pc::scan_exclusive(c->stream, dptr<int32_t>(c, B_ICNT), maxblocks,
-                              dptr<int32_t>(c, B_IOFF), dptr<int32_t>(c, B_SCANTMP)));
+    int32_t *items_dev = (int32_t *)(misc(c) + M_SIZES);
+    int32_t *nblk_dev = items_dev + 1;
+    // one pass of the work list kernel (see pc_launch.h)
+    auto list_pass = [&](int mode, pc_item *items, int32_t cap, unsigned *fl, int32_t *count) {
+        return pc::launch_items(c->stream, mode, (int32_t)nblocks, blocks, g, start2,
+                                dptr<int32_t>(c, B_CS1), autocorr ? 1 : 0, chunk,
+                                dptr<int32_t>(c, B_ICNT), dptr<int32_t>(c, B_IOFF), items, cap,
+                                fl, dptr<int32_t>(c, autocorr ? B_CS1 : B_CS2),
+                                (items && g.xy_local) ? dptr<int32_t>(c, B_ICELL) : nullptr,
+                                count, cand, nblk_dev);
+    };
+    if (ordered) {
+        HIPCHK(list_pass(0, nullptr, 0, nullptr, nullptr));
+        HIPCHK(pc::scan_exclusive(c->stream, dptr<int32_t>(c, B_ICNT), item_wgs,
+                                  dptr<int32_t>(c, B_IOFF), dptr<int32_t>(c, B_SCANTMP)));
+    }
     // Item count to the host (sizes the item array and the sweep launch);
     // a recorded call instead takes a fixed capacity and leaves the count
     // on the device, where the emit kernel and the sweep read it.
@@ -1253,13 +1269,18 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     } else if (async_items) {
         n_items = item_margin(c->last_items);
     } else {
-        HIPCHK(hipMemcpyAsync(pin + p_misc, dptr<int32_t>(c, B_IOFF) + maxblocks,
+        // (the counting pass adds the candidates and blocks too; the list's own
+        // pass counts them again)
+        if (!ordered)
+            HIPCHK(list_pass(2, nullptr, 0, nullptr, (int32_t *)(misc(c) + M_COUNTED)));
+        HIPCHK(hipMemcpyAsync(pin + p_misc,
+                              ordered ? dptr<int32_t>(c, B_IOFF) + item_wgs
+                                   : (int32_t *)(misc(c) + M_COUNTED),
                               sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipMemcpyAsync(pin + p_misc + 8, nblocks_dev, sizeof(int32_t),
-                              hipMemcpyDeviceToHost, c->stream));
+        if (!ordered)
+            HIPCHK(pc::launch_zero(c->stream, misc(c) + M_CAND, M_SIZES + 8 - M_CAND));
         HIPCHK(hipStreamSynchronize(c->stream));
         memcpy(&hcounts[0], pin + p_misc, 4);
-        memcpy(&hcounts[1], pin + p_misc + 8, 4);
         n_items = hcounts[0];
         if (n_items < 0)
             return fail(c, CF_EOVERFLOW, "work-item count overflow");
@@ -1270,12 +1291,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         return st2;
     // (the float32 sweep of 3-D grids takes each item's j column from the
     // cell of its first j point, written beside the items)
-    const int32_t *cs2_dev = dptr<int32_t>(c, autocorr ? B_CS1 : B_CS2);
-    HIPCHK(pc::launch_item_emit(c->stream, (int32_t)maxblocks, nblocks_dev,
-                                dptr<pc_block>(c, B_BLOCKS), g, start2, dptr<int32_t>(c, B_CS1),
-                                autocorr ? 1 : 0, chunk, dptr<int32_t>(c, B_IOFF),
-                                dptr<pc_item>(c, B_ITEMS), n_items, flags, cs2_dev,
-                                g.xy_local ? dptr<int32_t>(c, B_ICELL) : nullptr));
+    HIPCHK(list_pass(ordered ? 1 : 2, dptr<pc_item>(c, B_ITEMS), n_items, flags, items_dev));
     record(c, timing, 3);
 
     // ---- sweep -------------------------------------------------------------
@@ -1284,7 +1300,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     memset(&a, 0, sizeof(a));
     a.items = dptr<pc_item>(c, B_ITEMS);
     a.n_items = n_items;
-    a.n_items_dev = (ctl.capture || async_items) ? dptr<int32_t>(c, B_IOFF) + maxblocks : nullptr;
+    a.n_items_dev = (ctl.capture || async_items) ? items_dev : nullptr;
     a.counter = dptr<int32_t>(c, B_CTRS);
     a.X1 = dptr<float>(c, B_X1);
     a.Y1 = dptr<float>(c, B_Y1);
@@ -1474,9 +1490,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         HIPCHK(pc::launch_zero(c->stream, wsum, sizeof(double) * nout));
     HIPCHK(pc::launch_finalize(c->stream, ncat, (int32_t)nbt, autocorr ? 1 : 0, hb.hdr.e0_zero,
                                cats1_dev, a.g_hist, a.g_whist, a.g_rhist, wsq, a.g_wfix,
-                               wsq_fix, wfx, outc, outw, outr,
-                               dptr<int32_t>(c, B_IOFF) + maxblocks, nblocks_dev,
-                               (int32_t *)(misc(c) + M_SIZES)));
+                               wsq_fix, wfx, outc, outw, outr));
     char *hp = pin + p_out;
     HIPCHK(hipMemcpyAsync(pin + p_misc, misc(c), M_SIZE, hipMemcpyDeviceToHost, c->stream));
     if (!opt.output_on_device) {

@@ -597,10 +597,35 @@ __device__ __forceinline__ void store_sorted(const pc_grid &g, const double4 &r,
         wd[d] = r.w;
 }
 
+// ---- blocks of up to 64 points per column --------------------------------
+// Blocks of column c (sorted points [a, b)): its slots of the block array
+// start at a / 64 + c, which needs no scan of the columns' block counts (the
+// slots up to the next column's hold every block, and one empty block at
+// most).  Threads t, t + step, ... of the caller write them.
+__device__ __forceinline__ void put_blocks(pc_block *blocks, int c, int a, int b, int t, int step)
+{
+    const int o0 = a / PC_BLOCK_I + c, o1 = b / PC_BLOCK_I + c + 1;
+    for (int o = o0 + t; o < o1; o += step) {
+        pc_block blk;
+        blk.col = c;
+        blk.i0 = a + (o - o0) * PC_BLOCK_I;
+        blk.ni = max(min(PC_BLOCK_I, b - blk.i0), 0);
+        blk.pad = 0;
+        blocks[o] = blk;
+    }
+}
+
+__global__ void k_block_emit(int32_t ncol, int32_t nz, const int32_t *start, pc_block *blocks)
+{
+    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncol; c += gridDim.x * blockDim.x)
+        put_blocks(blocks, c, start[(int64_t)c * nz], start[(int64_t)(c + 1) * nz], 0, 1);
+}
+
 // Level 2: one workgroup per column sorts the column's points by z slice
 // (LDS counts and prefix) and writes the column's cell starts, the cell of
 // every sorted place and `perm`, the column-ordered index of the point that
-// goes there (k_gather then reads the records in sorted order).  The slice
+// goes there (k_gather then reads the records in sorted order), and (blocks
+// given) the column's blocks.  The slice
 // of a point is recomputed from its record with the same arithmetic as its
 // cell in k_cell_hist (point_cell), so it is the same value.
 constexpr int kSliceThreads = 1024;
@@ -610,7 +635,7 @@ template <bool SKY, bool GIVEN>
 __global__ __launch_bounds__(kSliceThreads) void k_slice_sort(
     int ncat, const int32_t *lay, int32_t ncolc, pc_grid g, const int32_t *__restrict__ woff,
     const double4 *__restrict__ colrec, int2 *__restrict__ rank_slice, int32_t *start,
-    int32_t *__restrict__ perm, int32_t *__restrict__ cell_sorted)
+    int32_t *__restrict__ perm, int32_t *__restrict__ cell_sorted, pc_block *blocks)
 {
     extern __shared__ unsigned sh[];
     const int nz = g.n[2];
@@ -620,6 +645,8 @@ __global__ __launch_bounds__(kSliceThreads) void k_slice_sort(
     const int cs = woff[mb + (int64_t)col * nw];
     const int ce = woff[mb + (int64_t)(col + 1) * nw];
     const int64_t cell0 = colall * nz;
+    if (blocks)
+        put_blocks(blocks, (int)colall, cs, ce, (int)threadIdx.x, kSliceThreads);
     for (int z = threadIdx.x; z < nz; z += blockDim.x)
         sh[z] = 0u;
     __syncthreads();
@@ -725,32 +752,6 @@ __global__ void k_gather(int64_t ntot, pc_grid g, const int32_t *perm, const int
     }
 }
 
-// ---- blocks of up to 64 points per column --------------------------------
-__global__ void k_block_count(int32_t ncol, int32_t nz, const int32_t *start, int32_t *bcnt)
-{
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncol; c += gridDim.x * blockDim.x) {
-        const int a = start[(int64_t)c * nz], b = start[(int64_t)(c + 1) * nz];
-        bcnt[c] = (b - a + PC_BLOCK_I - 1) / PC_BLOCK_I;
-    }
-}
-
-__global__ void k_block_emit(int32_t ncol, int32_t nz, const int32_t *start,
-                             const int32_t *boff, pc_block *blocks)
-{
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncol; c += gridDim.x * blockDim.x) {
-        const int a = start[(int64_t)c * nz], b = start[(int64_t)(c + 1) * nz];
-        int o = boff[c];
-        for (int i0 = a; i0 < b; i0 += PC_BLOCK_I, o++) {
-            pc_block blk;
-            blk.col = c;
-            blk.i0 = i0;
-            blk.ni = min(PC_BLOCK_I, b - i0);
-            blk.pad = 0;
-            blocks[o] = blk;
-        }
-    }
-}
-
 // ---- segments of one block ------------------------------------------------
 struct SegCtx {
     pc_grid g;
@@ -779,8 +780,10 @@ struct SegCtx {
 // outside zreach of the block's slices are skipped.  Autocorrelation visits
 // only cells after the block's own (a cell pair from its lower-numbered
 // cell), and the own cell forward along the sorted order.
+// Visit 0 is the block's own cell, visits 1 to 3 the bands below, level and
+// above; one thread makes one visit of one block.
 template <class F>
-__device__ void sky_segments(const SegCtx &c, const pc_block &b, F &&f)
+__device__ void sky_segments(const SegCtx &c, const pc_block &b, int visit, F &&f)
 {
     const int S = c.g.n[2], zr = c.g.zreach, nband = c.g.nband;
     const int ncolc = c.g.n[1];
@@ -798,20 +801,22 @@ __device__ void sky_segments(const SegCtx &c, const pc_block &b, F &&f)
     const int a = lcol - B.col0;
     const int sa = c.cell1_sorted[b.i0] % S;
     const int sb = c.cell1_sorted[b.i0 + b.ni - 1] % S;
-    if (c.autocorr) {
+    if (visit == 0) {
+        if (!c.autocorr)
+            return;
         if (b.ni > 1)
             f(b.i0 + 1, b.i0 + b.ni, 0u, 1);
         const int jend = c.start2[(int64_t)b.col * S + min(sb + zr, S - 1) + 1];
         if (jend > b.i0 + b.ni)
             f(b.i0 + b.ni, jend, 0u, 0);
-    }
-    for (int d = c.autocorr ? 0 : -1; d <= 1; d++) {
+    } else {
+        const int d = visit - 2;
         const int b2 = band + d;
-        if (b2 < 0 || b2 >= nband)
-            continue;
+        if (b2 < 0 || b2 >= nband || (d < 0 && c.autocorr))
+            return;
         const int a0 = max(sa - zr - d * S, 0), a1 = min(sb + zr - d * S, S - 1);
         if (a0 > a1)
-            continue;
+            return;
         const pc_band &C = c.g.bands[b2];
         const double D = d < 0 ? B.dra[0] : (d == 0 ? B.dra[1] : B.dra[2]);
         int k0 = 0, k1 = C.nra - 1;
@@ -837,11 +842,22 @@ __device__ void sky_segments(const SegCtx &c, const pc_block &b, F &&f)
     }
 }
 
-// KX > 0: the x/y refinement is KX (a compile-time constant, so the loops
-// over neighbour columns unroll and their cell-start loads are in flight
-// together); 0: read it from the grid.
-template <int KX, class F>
-__device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b, F &&f)
+// Visits of a block on a 3-D grid: autocorrelations its own column, then the
+// forward half of the column offsets within xyk, (0, 1..k) and (1..k, -k..k);
+// cross-correlations all (2 k + 1)^2 columns.  One thread makes one visit of
+// one block (a block's visits one after the other by one thread kept a handful
+// of waves busy on small catalogues, and each thread waiting for a chain of
+// loads).
+__host__ __device__ __forceinline__ int segment_visits(bool sky, int k, bool autocorr)
+{
+    if (sky)
+        return 4;
+    return autocorr ? 1 + k + k * (2 * k + 1) : (2 * k + 1) * (2 * k + 1);
+}
+
+template <class F>
+__device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b, int visit,
+                                              F &&f)
 {
     const int nx = c.g.n[0], ny = c.g.n[1], nz = c.g.n[2];
     // columns are numbered across catalogues: catalogue k owns columns
@@ -892,8 +908,10 @@ __device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b
         zwin(cbase + jx * ny + jy, code, zw);
     };
 
-    const int k = KX > 0 ? KX : c.g.xyk;
-    if (c.autocorr) {
+    const int k = c.g.xyk, side = 2 * k + 1;
+    if (!c.autocorr) {
+        column(visit / side - k, visit % side - k);
+    } else if (visit == 0) {
         // the block against itself (its triangle, j < i0 + ni) and its column
         // forward up to the reach: one contiguous segment flagged as holding
         // the triangle (the sweep masks only the chunks that reach into it)
@@ -906,95 +924,120 @@ __device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b
             const int w1 = min(hi_s - nz, nz - 1);
             f(c.start2[base], c.start2[base + w1 + 1], PC_D_MINUS << 4, 0);
         }
-        // the forward half of the offsets: (0, 1..k), then (1..k, -k..k)
-        for (int oy = 1; oy <= k; oy++)
-            column(0, oy);
-        for (int ox = 1; ox <= k; ox++)
-            for (int oy = -k; oy <= k; oy++)
-                column(ox, oy);
+    } else if (visit <= k) {
+        column(0, visit);
     } else {
-        for (int ox = -k; ox <= k; ox++)
-            for (int oy = -k; oy <= k; oy++)
-                column(ox, oy);
+        const int v = visit - 1 - k;
+        column(1 + v / side, v % side - k);
     }
 }
 
-template <bool SKY, class F>
-__device__ void for_each_segment(const SegCtx &c, const pc_block &b, F &&f)
+// Work items.  Thread t makes visit t % visits of block t / visits (a block's
+// items stay together in the list: the sweep keeps a block's points across
+// its items, and ran 5% slower on a list by visits): it counts the items of
+// its segments, the workgroup sums them, and the items go to
+//   MODE 0: nowhere; the workgroup's total to wcnt (ordered lists, first pass)
+//   MODE 1: the places after the scanned totals woff (second pass; the last
+//           workgroup leaves the list's length in n_items)
+//   MODE 2: places taken from n_items with one atomic per workgroup.
+// (The caller's comment says which list pays where.)
+// Items beyond `cap` are not written; the flag PC_FLAG_ITEMS reports them (a
+// repeated call whose inputs now need more items than it was built for).
+// cand and n_blocks (modes 0 and 2): candidate pairs and blocks.
+constexpr int kItemThreads = 256;
+template <bool SKY, int MODE>
+__global__ __launch_bounds__(kItemThreads) void k_items(
+    int32_t nblocks, int32_t visits, const pc_block *blocks, SegCtx c, int chunk, int32_t *wcnt,
+    const int32_t *woff, pc_item *items, int32_t cap, unsigned *flags, const int32_t *cs2,
+    int32_t *icell, int32_t *n_items, unsigned long long *cand, int32_t *n_blocks)
 {
-    if constexpr (SKY) {
-        sky_segments(c, b, f);
-    } else {
-        if (c.g.xyk == 1)
-            grid_segments<1>(c, b, f);
-        else
-            grid_segments<0>(c, b, f);
-    }
-}
-
-template <bool SKY>
-__global__ void k_item_count(int32_t nblocks, const int32_t *nblocks_dev,
-                             const pc_block *blocks, SegCtx c, int chunk, int32_t *icnt,
-                             unsigned long long *cand)
-{
-    const int nb = nblocks_dev ? *nblocks_dev : nblocks;
+    const unsigned long long t0 = (unsigned long long)blockIdx.x * kItemThreads;
+    const unsigned tr = (unsigned)(t0 % (unsigned)visits) + threadIdx.x;
+    const int bi = (int)(t0 / (unsigned)visits) + (int)(tr / (unsigned)visits);
+    const int visit = (int)(tr % (unsigned)visits);
+    const int wg = (int)blockIdx.x;
+    pc_block b;
+    b.ni = 0;
+    if (bi < nblocks)
+        b = blocks[bi];
+    auto segments = [&](auto &&f) {
+        if (b.ni > 0) {
+            if constexpr (SKY)
+                sky_segments(c, b, visit, f);
+            else
+                grid_segments(c, b, visit, f);
+        }
+    };
+    int total = 0;
     unsigned long long my = 0;
-    for (int bi = blockIdx.x * blockDim.x + threadIdx.x; bi < nb;
-         bi += gridDim.x * blockDim.x) {
-        const pc_block b = blocks[bi];
-        int total = 0;
-        for_each_segment<SKY>(c, b, [&](int j0, int j1, unsigned, int tri) {
-            if (j1 <= j0)
-                return;
-            total += (j1 - j0 + chunk - 1) / chunk;
-            // a triangle segment: the block's unique pairs with itself, then
-            // every j beyond the block (j1 >= i0 + ni)
-            my += tri ? (unsigned long long)b.ni * (b.ni - 1) / 2 +
-                            (unsigned long long)b.ni * (unsigned long long)(j1 - b.i0 - b.ni)
-                      : (unsigned long long)b.ni * (unsigned long long)(j1 - j0);
-        });
-        icnt[bi] = total;
-    }
-    // one atomic per wave: a per-thread add to the one counter serialises
-    // every block of the work list at one L2 address
-    for (int off = PC_WAVE / 2; off > 0; off >>= 1)
-        my += __shfl_xor(my, off);
-    if ((threadIdx.x & (PC_WAVE - 1)) == 0 && my)
-        atomicAdd(cand, my);
-}
-
-// Items beyond `cap` are not written; the flag PC_FLAG_ITEMS reports them
-// (a replayed call whose inputs now need more items than it was built for).
-template <bool SKY>
-__global__ void k_item_emit(int32_t nblocks, const int32_t *nblocks_dev, const pc_block *blocks,
-                            SegCtx c, int chunk, const int32_t *ioff, pc_item *items, int32_t cap,
-                            unsigned *flags, const int32_t *cs2, int32_t *icell)
-{
-    const int nb = nblocks_dev ? *nblocks_dev : nblocks;
-    for (int bi = blockIdx.x * blockDim.x + threadIdx.x; bi < nb;
-         bi += gridDim.x * blockDim.x) {
-        const pc_block b = blocks[bi];
-        const int cat = b.col / (c.g.n[0] * c.g.n[1]);
-        int o = ioff[bi];
-        for_each_segment<SKY>(c, b, [&](int j0, int j1, unsigned dcode, int tri) {
-            for (int j = j0; j < j1; j += chunk) {
-                pc_item it;
-                it.i0 = b.i0;
-                it.j0 = j;
-                it.j1 = min(j + chunk, j1);
-                it.meta = (unsigned)(b.ni - 1) | (dcode << 6) | ((unsigned)tri << 12) |
-                          ((unsigned)cat << 13);
-                if (o < cap) {
-                    items[o] = it;
-                    if (icell)
-                        icell[o] = cs2[j];
-                }
-                o++;
+    segments([&](int j0, int j1, unsigned, int tri) {
+        if (j1 <= j0)
+            return;
+        total += (j1 - j0 + chunk - 1) / chunk;
+        // a triangle segment: the block's unique pairs with itself, then
+        // every j beyond the block (j1 >= i0 + ni)
+        my += tri ? (unsigned long long)b.ni * (b.ni - 1) / 2 +
+                        (unsigned long long)b.ni * (unsigned long long)(j1 - b.i0 - b.ni)
+                  : (unsigned long long)b.ni * (unsigned long long)(j1 - j0);
+    });
+    int sum;
+    int o = block_exclusive_waves<kItemThreads>(total, &sum);
+    __shared__ int s_base;
+    if constexpr (MODE != 1) {
+        __shared__ unsigned long long s_cand[kItemThreads / PC_WAVE];
+        __shared__ int s_blk[kItemThreads / PC_WAVE];
+        int nb = visit == 0 && b.ni > 0 ? 1 : 0;
+        for (int off = PC_WAVE / 2; off > 0; off >>= 1) {
+            my += __shfl_xor(my, off);
+            nb += __shfl_xor(nb, off);
+        }
+        if ((threadIdx.x & (PC_WAVE - 1)) == 0) {
+            s_cand[threadIdx.x / PC_WAVE] = my;
+            s_blk[threadIdx.x / PC_WAVE] = nb;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kItemThreads / PC_WAVE; w++) {
+                my += s_cand[w];
+                nb += s_blk[w];
             }
-        });
-        if (o > cap)
-            atomicOr(flags, PC_FLAG_ITEMS);
+            if (my)
+                atomicAdd(cand, my);
+            if (nb)
+                atomicAdd(n_blocks, nb);
+            if (MODE == 0)
+                wcnt[wg] = sum;
+            else
+                s_base = sum ? atomicAdd(n_items, sum) : 0;
+        }
+        if (MODE == 0)
+            return;
+    } else if (threadIdx.x == 0) {
+        s_base = woff[wg];
+        if (wg == 0)
+            *n_items = woff[gridDim.x];
     }
+    __syncthreads();
+    o += s_base;
+    const int cat = b.ni > 0 ? b.col / (c.g.n[0] * c.g.n[1]) : 0;
+    segments([&](int j0, int j1, unsigned dcode, int tri) {
+        for (int j = j0; j < j1; j += chunk) {
+            pc_item it;
+            it.i0 = b.i0;
+            it.j0 = j;
+            it.j1 = min(j + chunk, j1);
+            it.meta = (unsigned)(b.ni - 1) | (dcode << 6) | ((unsigned)tri << 12) |
+                      ((unsigned)cat << 13);
+            if (o < cap) {
+                items[o] = it;
+                if (icell)
+                    icell[o] = cs2[j];
+            }
+            o++;
+        }
+    });
+    if (flags && total && o > cap)
+        atomicOr(flags, PC_FLAG_ITEMS);
 }
 
 // ---- lookup table of the decision bands -------------------------------------
@@ -1209,7 +1252,7 @@ hipError_t launch_sort2(hipStream_t s, int ncat, const pc_cat *cats, int64_t nto
                         int32_t *cell_of, int32_t *rank_of, void *colrec, void *rank_slice,
                         int32_t *perm, int32_t *start, int32_t *cell_sorted, float *X, float *Y,
                         float *Z, double *xd, double *yd, double *zd, double *wd, float4 *P,
-                        unsigned *flags)
+                        unsigned *flags, pc_block *blocks)
 {
     double4 *cr = static_cast<double4 *>(colrec);
     hipLaunchKernelGGL(k_grid_layout, dim3(1), dim3(64), 0, s, ncat, cats, chunk, ncolc, lay);
@@ -1241,52 +1284,44 @@ hipError_t launch_sort2(hipStream_t s, int ncat, const pc_cat *cats, int64_t nto
                                             : k_slice_sort<false, false>),
                        dim3((unsigned)((int64_t)ncat * ncolc)), dim3(kSliceThreads),
                        sizeof(unsigned) * (size_t)g.n[2], s, ncat, lay, ncolc, g, woff, cr,
-                       static_cast<int2 *>(rank_slice), start, perm, cell_sorted);
+                       static_cast<int2 *>(rank_slice), start, perm, cell_sorted, blocks);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     return launch_gather(s, ntot, g, perm, nullptr, colrec, X, Y, Z, xd, yd, zd, wd, P,
                          cell_sorted);
 }
 
-hipError_t launch_block_count(hipStream_t s, int32_t ncol, int32_t nz, const int32_t *start,
-                              int32_t *bcnt)
-{
-    hipLaunchKernelGGL(k_block_count, dim3(grid_for(ncol)), dim3(kThreads), 0, s, ncol, nz,
-                       start, bcnt);
-    return hipGetLastError();
-}
-
 hipError_t launch_block_emit(hipStream_t s, int32_t ncol, int32_t nz, const int32_t *start,
-                             const int32_t *boff, pc_block *blocks)
+                             pc_block *blocks)
 {
     hipLaunchKernelGGL(k_block_emit, dim3(grid_for(ncol, 64)), dim3(64), 0, s, ncol, nz, start,
-                       boff, blocks);
+                       blocks);
     return hipGetLastError();
 }
 
-hipError_t launch_item_count(hipStream_t s, int32_t nblocks, const int32_t *nblocks_dev,
-                             const pc_block *blocks, const pc_grid &g, const int32_t *start2,
-                             const int32_t *cell1_sorted, int autocorr, int chunk,
-                             int32_t *icnt, unsigned long long *cand)
+int64_t item_workgroups(int64_t nblocks, const pc_grid &g, int autocorr)
 {
-    SegCtx c{g, start2, cell1_sorted, autocorr};
-    hipLaunchKernelGGL(g.nband > 0 ? k_item_count<true> : k_item_count<false>,
-                       dim3(grid_for(nblocks, 128)), dim3(128), 0, s, nblocks,
-                       nblocks_dev, blocks, c, chunk, icnt, cand);
-    return hipGetLastError();
+    const int64_t t = nblocks * segment_visits(g.nband > 0, g.xyk, autocorr != 0);
+    return std::max<int64_t>((t + kItemThreads - 1) / kItemThreads, 1);
 }
 
-hipError_t launch_item_emit(hipStream_t s, int32_t nblocks, const int32_t *nblocks_dev,
-                            const pc_block *blocks, const pc_grid &g, const int32_t *start2,
-                            const int32_t *cell1_sorted, int autocorr, int chunk,
-                            const int32_t *ioff, pc_item *items, int32_t cap, unsigned *flags,
-                            const int32_t *cell2_sorted, int32_t *icell)
+hipError_t launch_items(hipStream_t s, int mode, int32_t nblocks, const pc_block *blocks,
+                        const pc_grid &g, const int32_t *start2, const int32_t *cell1_sorted,
+                        int autocorr, int chunk, int32_t *wcnt, const int32_t *woff,
+                        pc_item *items, int32_t cap, unsigned *flags,
+                        const int32_t *cell2_sorted, int32_t *icell, int32_t *n_items,
+                        unsigned long long *cand, int32_t *n_blocks)
 {
     SegCtx c{g, start2, cell1_sorted, autocorr};
-    hipLaunchKernelGGL(g.nband > 0 ? k_item_emit<true> : k_item_emit<false>,
-                       dim3(grid_for(nblocks, 128)), dim3(128), 0, s, nblocks,
-                       nblocks_dev, blocks, c, chunk, ioff, items, cap, flags, cell2_sorted,
-                       icell);
+    const bool sky = g.nband > 0;
+    const int visits = segment_visits(sky, g.xyk, autocorr != 0);
+    auto fn = mode == 0 ? (sky ? k_items<true, 0> : k_items<false, 0>)
+                        : mode == 1 ? (sky ? k_items<true, 1> : k_items<false, 1>)
+                                    : (sky ? k_items<true, 2> : k_items<false, 2>);
+    hipLaunchKernelGGL(fn,
+                       dim3((unsigned)item_workgroups(nblocks, g, autocorr)),
+                       dim3(kItemThreads), 0, s, nblocks, visits, blocks, c, chunk, wcnt, woff, items, cap,
+                       flags, cell2_sorted, icell, n_items, cand, n_blocks);
     return hipGetLastError();
 }
 

@@ -129,7 +129,8 @@ hipError_t launch_gather(hipStream_t s, int64_t ntot, const pc_grid &g, const in
 // yd, zd and (optional) wd, like launch_cell_index + scan + launch_scatter.
 // Needs ncolc and g.n[2] at most PC_SORT2_MAX_BINS; `lay` holds 3 (ncat + 1)
 // ints, wcnt m ints, woff m + 1 ints (m = sum over catalogues of ncolc *
-// chunks), tmp scan_tmp_elems(m) ints; scratch: colrec ntot 32-byte records
+// chunks), tmp scan_tmp_elems(m) ints; blocks (or NULL): receives the blocks
+// (launch_block_emit); scratch: colrec ntot 32-byte records
 // (column order), rank_slice ntot int pairs, perm, cell_of and rank_of ntot
 // ints each.
 #define PC_SORT2_MAX_BINS 16384
@@ -139,23 +140,28 @@ hipError_t launch_sort2(hipStream_t s, int ncat, const pc_cat *cats, int64_t nto
                         int32_t *cell_of, int32_t *rank_of, void *colrec, void *rank_slice,
                         int32_t *perm, int32_t *start, int32_t *cell_sorted, float *X, float *Y,
                         float *Z, double *xd, double *yd, double *zd, double *wd, float4 *P,
-                        unsigned *flags);
-hipError_t launch_block_count(hipStream_t s, int32_t ncol, int32_t nz, const int32_t *start,
-                              int32_t *bcnt);
+                        unsigned *flags, pc_block *blocks);
+// blocks of up to 64 sorted points of every column, at places (first sorted
+// point) / 64 + column: n / 64 + ncol places hold them all, some with ni = 0
+// (launch_sort2 writes them itself when asked to)
 hipError_t launch_block_emit(hipStream_t s, int32_t ncol, int32_t nz, const int32_t *start,
-                             const int32_t *boff, pc_block *blocks);
-hipError_t launch_item_count(hipStream_t s, int32_t nblocks, const int32_t *nblocks_dev,
-                             const pc_block *blocks, const pc_grid &g, const int32_t *start2,
-                             const int32_t *cell1_sorted, int autocorr, int chunk,
-                             int32_t *icnt, unsigned long long *cand);
-// icell (optional, with cell2_sorted): the cell id of every item's first j
-// point, beside the items (the float32 sweep of 3-D grids reads it one item
-// ahead, with the item, to place its lanes in the j column's frame)
-hipError_t launch_item_emit(hipStream_t s, int32_t nblocks, const int32_t *nblocks_dev,
-                            const pc_block *blocks, const pc_grid &g, const int32_t *start2,
-                            const int32_t *cell1_sorted, int autocorr, int chunk,
-                            const int32_t *ioff, pc_item *items, int32_t cap, unsigned *flags,
-                            const int32_t *cell2_sorted, int32_t *icell);
+                             pc_block *blocks);
+// Work items of `nblocks` block places.  mode 0: counts per workgroup to wcnt
+// (item_workgroups of them); mode 1: items to the places after woff, the scan
+// of those counts, and the list's length to n_items; mode 2: items to places
+// taken from n_items (zeroed first) in one pass.  At most `cap` items are
+// written (PC_FLAG_ITEMS in flags, unless NULL, when there are more).  cand and
+// n_blocks (zeroed first; modes 0 and 2) receive the candidate pairs and the
+// blocks.  icell (optional, with cell2_sorted): the cell id of every item's
+// first j point, beside the items (the float32 sweep of 3-D grids reads it one
+// item ahead, with the item, to place its lanes in the j column's frame).
+int64_t item_workgroups(int64_t nblocks, const pc_grid &g, int autocorr);
+hipError_t launch_items(hipStream_t s, int mode, int32_t nblocks, const pc_block *blocks,
+                        const pc_grid &g, const int32_t *start2, const int32_t *cell1_sorted,
+                        int autocorr, int chunk, int32_t *wcnt, const int32_t *woff,
+                        pc_item *items, int32_t cap, unsigned *flags,
+                        const int32_t *cell2_sorted, int32_t *icell, int32_t *n_items,
+                        unsigned long long *cand, int32_t *n_blocks);
 // wmode: 0 unweighted, 1 weight sums, 2 weight and mean-separation sums
 hipError_t launch_sweep(hipStream_t s, int metric, bool fp32, int wmode, const SweepArgs &a,
                         int nwg);
@@ -177,15 +183,13 @@ hipError_t launch_wsq_fixed(hipStream_t s, int32_t ncat, int64_t ncell, const in
 // counts (and weight sums, mean separations) of every catalogue: doubling
 // and self-pairs of autocorrelations; the mean separation is the separation
 // sum over the weight sum
-// (it also copies the device work-item and block counts to `sizes_out`)
 hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
                            const pc_cat *cats, const unsigned long long *g_hist,
                            const double *g_whist, const double *g_rhist, const double *wsq,
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
-                           double *out_ravg, const int32_t *n_items_dev,
-                           const int32_t *n_blocks_dev, int32_t *sizes_out);
+                           double *out_ravg);
 // resident sweep workgroups per CU for a dynamic LDS size
 // waves per sweep workgroup
 int sweep_waves();
