@@ -1132,10 +1132,10 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // in which its workgroups finish, which saves the counting pass and the
     // scan.  Block order keeps a wave's successive items on the same j points:
     // without it the sweep is 2% slower on 10^6 points and 9% on 1.5*10^5 by
-    // 6*10^5 cross points (437 -> 475 us, for 6 us saved here), but no slower
-    // up to 10^5, where the list takes 15 us in place of 24.  (Batched calls
-    // meet their catalogues one after the other.)
-    const bool ordered = priv || n1 + (autocorr ? 0 : n2) > 131072;
+    // 6*10^5 cross points (437 -> 475 us, for 6 us saved here), 30% on 1.15*10^5
+    // (88 -> 115 us), but no slower at 6.6*10^4, where the list takes 15 us in
+    // place of 24.  (Batched calls meet their catalogues one after the other.)
+    const bool ordered = priv || n1 + (autocorr ? 0 : n2) > 65536;
     const int chunk = opt.chunk > 0 ? std::min(opt.chunk, 1 << 20) : 2048;
     if ((st2 = ensure(c, B_BLOCKS, sizeof(pc_block) * (size_t)nblocks)) ||
         (ordered && (st2 = ensure(c, B_ICNT, sizeof(int32_t) * (size_t)item_wgs))) ||

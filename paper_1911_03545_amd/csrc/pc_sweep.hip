@@ -1078,6 +1078,11 @@ __device__ __forceinline__ int tri_end(int j0, int j1, int iend)
 // reads one word to know the streams that may still hold items, instead of
 // one counter after the other (64 round trips after a wave's last item).
 static_assert(PC_STREAMS == 64, "one bit per stream");
+// first item of stream s: s n / 64, in 32-bit steps
+__device__ __forceinline__ int stream_first(int n, int s)
+{
+    return (n >> 6) * s + (((n & 63) * s) >> 6);
+}
 __device__ __forceinline__ int wave_fetch(int *ctrs, int n_items, int lane, int &s, bool &probe)
 {
     unsigned long long *done =
@@ -1099,8 +1104,7 @@ __device__ __forceinline__ int wave_fetch(int *ctrs, int n_items, int lane, int 
             const unsigned long long rot = r ? (open >> r) | (open << (PC_STREAMS - r)) : open;
             s = (r + __ffsll((long long)rot) - 1) & (PC_STREAMS - 1);
         }
-        const int first = (int)(((long long)n_items * s) / PC_STREAMS);
-        const int len = (int)(((long long)n_items * (s + 1)) / PC_STREAMS) - first;
+        const int first = stream_first(n_items, s), len = stream_first(n_items, s + 1) - first;
         int v = 0;
         if (lane == 0) {
             v = atomicAdd(ctrs + s * PC_STREAM_STRIDE, 1);
@@ -1298,17 +1302,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     // the float32 loop's lane point, kept while consecutive items share a block
     int lp_i0 = -1, lp_ni = -1;
     LanePt lp = {0.0, 0.0, 0.0, 0.0, 0.0f, 0.0f, 0.0f};
-    int next = wave_fetch(a.counter, n_items, lane, stream, probe);
     pc_item nit = {};
     // (3-D grids: the cell of the next item's first j point, read with the
     // item so that its column is known when the item starts)
     const KCONST int32_t *icell = (const KCONST int32_t *)a.icell;
     int ncell = 0;
-    if (P32 && next < n_items) {
-        nit = a.items[next];
-        if (a.xy_local)
-            ncell = icell[next];
-    }
     // Unweighted float32 r sweeps of one catalogue also start the take of the
     // item after the next one before running an item (one atomic increment
     // on the wave's stream, `pend`), read its result only at the next item
@@ -1323,31 +1321,37 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     constexpr bool AHEAD = PIPE || (P32 && PRIV);
     int pv = 0;
     bool pend = false;
-    while (next < n_items) {
-        // float32 sweeps load the following item's descriptor while this
-        // item runs (measured slower for the binary64 sweep, which keeps the
-        // load after the take)
+    // One take per turn, of the item after the turn's own (the first turn only
+    // takes): wave_fetch has one place in the code (three copies of it spilled
+    // scalar registers into the rp/pi loops and cost the weighted ones 7%).
+    int next = -1;
+    for (;;) {
+        if (next >= n_items)
+            break;
         const int cur = next;
-        const pc_item it = P32 ? nit : a.items[cur];
+        const pc_item cit = nit;
         const int jcell = ncell;
+        bool take = true;
         if (AHEAD && pend) {
             pend = false;
-            const int first = (int)(((long long)n_items * stream) / PC_STREAMS);
-            const int len = (int)(((long long)n_items * (stream + 1)) / PC_STREAMS) - first;
+            const int first = stream_first(n_items, stream);
+            const int len = stream_first(n_items, stream + 1) - first;
             const int v = __builtin_amdgcn_readfirstlane(pv);
-            if (v < len) {
-                next = first + v;
-            } else {
+            take = v >= len;
+            next = first + v;
+            if (take) {
                 if (v == len && lane == 0)
                     atomicOr(reinterpret_cast<unsigned long long *>(
                                  a.counter + PC_STREAMS * PC_STREAM_STRIDE),
                              1ull << stream);
                 probe = true;
-                next = wave_fetch(a.counter, n_items, lane, stream, probe);
             }
-        } else {
-            next = wave_fetch(a.counter, n_items, lane, stream, probe);
         }
+        if (take)
+            next = wave_fetch(a.counter, n_items, lane, stream, probe);
+        // float32 sweeps load the following item's descriptor while this
+        // item runs (measured slower for the binary64 sweep, which loads it
+        // after the take)
         if (P32 && next < n_items) {
             nit = a.items[next];
             if (a.xy_local)
@@ -1358,6 +1362,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 pv = atomicAdd(a.counter + stream * PC_STREAM_STRIDE, 1);
             pend = true;
         }
+        if (cur < 0)
+            continue;
+        const pc_item it = P32 ? cit : a.items[cur];
         const int ni = (int)PC_META_NI(it.meta);
         const unsigned dcode = PC_META_DCODE(it.meta);
         const bool tri = PC_META_TRI(it.meta) != 0;
