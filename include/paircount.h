@@ -108,7 +108,8 @@ typedef struct cf_options {
     int32_t slices_per_reach;   /* z slices per line-of-sight reach (0: 32;
                                    declination slices per band on the angular
                                    grid)                                       */
-    int32_t chunk;              /* max j points per work item (default 2048)   */
+    int32_t chunk;              /* max j points per work item (default 2048;
+                                   short work lists take shorter items)       */
     int32_t output_on_device;   /* counts / wsum are device pointers           */
     int32_t theta_unit_vectors; /* theta input is unit vectors, not RA/DEC;
                                    on-sky (mocks) input is Cartesian positions,
@@ -243,7 +244,7 @@ typedef struct cf_stats {
     float t_finalize_ms;        /* doubling, self-pairs, copy-out              */
     float t_total_ms;           /* whole call, first to last event             */
     int32_t slices_per_reach;   /* z slices per reach used (after autotuning)  */
-    int32_t chunk;              /* max j points per work item used             */
+    int32_t chunk;              /* max j points per work item allowed          */
     int32_t replayed;           /* 1 when the call replayed a recorded graph   */
     int32_t angular_grid;       /* angular grid refinement used (0: 3-D cells) */
     int32_t xy_refine;          /* x/y refinement of a 3-D grid (0: angular)   */

@@ -1123,6 +1123,12 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     g.fscale = fscale;
     record(c, timing, 1);
 
+    // sets of global bins that the sweep's workgroups merge into: the binary64
+    // sums of up to 768 workgroups otherwise queue at the same bins (850 ->
+    // 777 us of 10^6 weighted (rp, pi) points with mean separations); counts
+    // alone measured no faster with them
+    const int hsets = !priv && weighted ? 8 : 1;
+    const size_t nhist = nout * (size_t)hsets;
     // ---- work-list and sweep buffers, cleared by one kernel ahead of the
     // gridding (the host issues it while nothing else waits on it) ----------
     const int32_t ncol = g.n[0] * g.n[1] * ncat;   // columns of every catalogue
@@ -1136,17 +1142,39 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // (88 -> 115 us), but no slower at 6.6*10^4, where the list takes 15 us in
     // place of 24.  (Batched calls meet their catalogues one after the other.)
     const bool ordered = priv || n1 + (autocorr ? 0 : n2) > 65536;
-    const int chunk = opt.chunk > 0 ? std::min(opt.chunk, 1 << 20) : 2048;
+    const int chunk_max = opt.chunk > 0 ? std::min(opt.chunk, 1 << 20) : 2048;
+    int chunk = chunk_max;
+    if (!priv && !sky_grid && opt.flush_pairs == 0) {
+        // (a caller that lowers the merge bound wants waves to reach it)
+        // Shorter items where the whole list is short: about two items for
+        // each resident wave (eight with weights, whose pairs take longer),
+        // from the expected length of a neighbour column's z window, but no
+        // shorter than 64 points (an item's own cost).  A wave takes its points
+        // one chunk after the other, so a short list of long items waits for
+        // its longest: sweeps of 10^5 points in binary64 150 -> 97 us, of
+        // 2.8*10^4 (rp, pi) points 82 -> 51, of 1.5*10^5 by 6*10^5 weighted
+        // points 437 -> 370, of 3*10^5 weighted (rp, pi) points with mean
+        // separations 1770 -> 1470 us; 10^6 points stay at 2048 (with 256: 587
+        // -> 616).
+        const double ncolc = (double)g.n[0] * g.n[1];
+        const double win = std::min(1.0, (2.0 * g.zreach + 1.0) / g.n[2]);
+        const double run_len = (double)n2 / ncolc * win + PC_BLOCK_I;
+        const double js = run_len * (double)(n1 / PC_BLOCK_I + ncol) *
+                          (autocorr ? 0.5 : 1.0) * (2 * g.xyk + 1) * (2 * g.xyk + 1);
+        const double each = js / ((weighted ? 8.0 : 2.0) * 32.0 * c->num_cu);
+        if (each < chunk)
+            chunk = std::max(std::min(chunk, 64), ((int)each + 7) / 8 * 8);
+    }
     if ((st2 = ensure(c, B_BLOCKS, sizeof(pc_block) * (size_t)nblocks)) ||
         (ordered && (st2 = ensure(c, B_ICNT, sizeof(int32_t) * (size_t)item_wgs))) ||
         (ordered && (st2 = ensure(c, B_IOFF, sizeof(int32_t) * (size_t)(item_wgs + 1)))) ||
         (st2 = ensure(c, B_SCANTMP, sizeof(int32_t) * pc::scan_tmp_elems(std::max<int64_t>(
                                         item_wgs, (int64_t)ncat * g.ncell)))) ||
-        (st2 = ensure(c, B_HIST, sizeof(unsigned long long) * nout)) ||
-        (st2 = ensure(c, B_WHIST, (wfixed ? 24 : 8) * nout)) ||
+        (st2 = ensure(c, B_HIST, sizeof(unsigned long long) * nhist)) ||
+        (st2 = ensure(c, B_WHIST, (wfixed ? 24 : 8) * nhist)) ||
         (st2 = ensure(c, B_OUTC, sizeof(unsigned long long) * nout)) ||
         (st2 = ensure(c, B_OUTW, sizeof(double) * nout)) ||
-        (want_ravg && (st2 = ensure(c, B_RHIST, sizeof(double) * nout))) ||
+        (want_ravg && (st2 = ensure(c, B_RHIST, sizeof(double) * nhist))) ||
         (want_ravg && (st2 = ensure(c, B_OUTR, sizeof(double) * nout))) ||
         (st2 = ensure(c, B_WSQ, (wfixed ? 24 : 8) * (size_t)ncat)) ||
         (st2 = ensure(c, B_CTRS, PC_STREAM_BYTES)))
@@ -1158,14 +1186,14 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         zp[nz] = c->buf[B_CTRS].p;
         zb[nz++] = PC_STREAM_BYTES;
         zp[nz] = c->buf[B_HIST].p;
-        zb[nz++] = sizeof(unsigned long long) * nout;
+        zb[nz++] = sizeof(unsigned long long) * nhist;
         if (weighted) {
             zp[nz] = c->buf[B_WHIST].p;
-            zb[nz++] = (wfixed ? 24 : 8) * nout;
+            zb[nz++] = (wfixed ? 24 : 8) * nhist;
         }
         if (want_ravg) {
             zp[nz] = c->buf[B_RHIST].p;
-            zb[nz++] = sizeof(double) * nout;
+            zb[nz++] = sizeof(double) * nhist;
         }
         HIPCHK(pc::launch_zero_multi(c->stream, nz, zp, zb));
     }
@@ -1362,6 +1390,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     a.cs2 = autocorr ? dptr<int32_t>(c, B_CS1) : dptr<int32_t>(c, B_CS2);
     a.icell = g.xy_local ? dptr<int32_t>(c, B_ICELL) : nullptr;
     a.nbt = (int32_t)nbt;
+    a.hsets = hsets;
     a.slots = (int32_t)((nb + 2) * hb.hdr.row_w);
     a.priv = priv ? 1 : 0;
     // replica stride: odd, so the lanes' copies of one slot spread over banks
@@ -1490,7 +1519,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         HIPCHK(pc::launch_zero(c->stream, wsum, sizeof(double) * nout));
     HIPCHK(pc::launch_finalize(c->stream, ncat, (int32_t)nbt, autocorr ? 1 : 0, hb.hdr.e0_zero,
                                cats1_dev, a.g_hist, a.g_whist, a.g_rhist, wsq, a.g_wfix,
-                               wsq_fix, wfx, outc, outw, outr));
+                               wsq_fix, wfx, outc, outw, outr, hsets));
     char *hp = pin + p_out;
     HIPCHK(hipMemcpyAsync(pin + p_misc, misc(c), M_SIZE, hipMemcpyDeviceToHost, c->stream));
     if (!opt.output_on_device) {
@@ -1574,7 +1603,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     S.angular_grid = opt.angular_grid;
     S.xy_refine = sky_grid ? 0 : g.xyk;
     S.separation_form = fp32 ? (xy_mag > 0.0 ? 2 : 1) : 0;
-    S.chunk = chunk;
+    S.chunk = chunk_max;
     S.n_blocks = hcounts[1];
     S.n_items = hcounts[0];
     S.candidate_pairs = cnd;

@@ -39,6 +39,10 @@ struct SweepArgs {
     int32_t wlimb;
     const pc_wfixed *wfx;
     unsigned long long *g_wfix;
+    // sets of global bins (power of two; 1 for batches): workgroup b merges into
+    // set b mod hsets.  1024 workgroups adding to the same 20 bins queue at a
+    // handful of addresses for longer than a small call's pairs take.
+    int32_t hsets;
     double *g_rhist;       // sums of separation x pair weight (mean separation), or NULL
     int32_t ravg;          // 0: no mean separation; 1: distance sqrt(s);
                            // 2: angle in degrees of a squared chord s
@@ -189,7 +193,7 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
-                           double *out_ravg);
+                           double *out_ravg, int32_t hsets);
 // resident sweep workgroups per CU for a dynamic LDS size
 // waves per sweep workgroup
 int sweep_waves();

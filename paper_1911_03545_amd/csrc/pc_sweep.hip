@@ -1141,6 +1141,9 @@ __device__ __forceinline__ void flush_hist(const SweepArgs &a, const Lds &L, int
                                            bool W, unsigned cat)
 {
     const int npi = a.B.npi, rw = a.B.row_w, c0 = a.B.col0;
+    // (a single catalogue's merges are spread over a.hsets sets of bins)
+    if (a.hsets > 1)
+        cat = blockIdx.x & (unsigned)(a.hsets - 1);
     unsigned long long *gh = a.g_hist + (size_t)cat * a.nbt;
     double *gw = W ? a.g_whist + (size_t)cat * a.nbt : nullptr;
     // mean-separation sums: a second set of replicas after the weight sums
@@ -1324,13 +1327,16 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     // One take per turn, of the item after the turn's own (the first turn only
     // takes): wave_fetch has one place in the code (three copies of it spilled
     // scalar registers into the rp/pi loops and cost the weighted ones 7%).
+    // Short lists (fewer than four items a wave) are not taken ahead: a wave
+    // that starts early would hold two or three items while others find none.
+    const bool late = n_items < 4 * kWaves * (int)gridDim.x;
     int next = -1;
     for (;;) {
         if (next >= n_items)
             break;
-        const int cur = next;
-        const pc_item cit = nit;
-        const int jcell = ncell;
+        int cur = next;
+        pc_item cit = nit;
+        int jcell = ncell;
         bool take = true;
         if (AHEAD && pend) {
             pend = false;
@@ -1357,13 +1363,20 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             if (a.xy_local)
                 ncell = icell[next];
         }
-        if (AHEAD && next < n_items && !probe) {
+        if (AHEAD && next < n_items && !probe && !late) {
             if (lane == 0)
                 pv = atomicAdd(a.counter + stream * PC_STREAM_STRIDE, 1);
             pend = true;
         }
-        if (cur < 0)
+        if (late) {
+            if (next >= n_items)
+                break;
+            cur = next;
+            cit = nit;
+            jcell = ncell;
+        } else if (cur < 0) {
             continue;
+        }
         const pc_item it = P32 ? cit : a.items[cur];
         const int ni = (int)PC_META_NI(it.meta);
         const unsigned dcode = PC_META_DCODE(it.meta);
@@ -1622,7 +1635,8 @@ __global__ void k_finalize(int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
                            const double *g_whist, const double *g_rhist, const double *wsq,
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
-                           unsigned long long *out_counts, double *out_wsum, double *out_ravg)
+                           unsigned long long *out_counts, double *out_wsum, double *out_ravg,
+                           int32_t hsets)
 {
     const int64_t total = (int64_t)ncat * nbt;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
@@ -1630,6 +1644,17 @@ __global__ void k_finalize(int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
         const int c = (int)(t / nbt), b = (int)(t % nbt);
         unsigned long long v = g_hist[t];
         double w = g_whist ? g_whist[t] : 0.0;
+        double rs = g_rhist ? g_rhist[t] : 0.0;
+        // (several sets: one catalogue only, set s holds its bins at s nbt)
+#pragma unroll 8
+        for (int s = 1; s < hsets; s++) {
+            const int64_t u = t + (int64_t)s * nbt;
+            v += g_hist[u];
+            if (g_whist)
+                w += g_whist[u];
+            if (g_rhist)
+                rs += g_rhist[u];
+        }
         if (autocorr) {
             v *= 2ull;
             w *= 2.0;
@@ -1641,6 +1666,12 @@ __global__ void k_finalize(int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
         }
         if (g_wfix) {
             unsigned long long f[3] = {g_wfix[3 * t], g_wfix[3 * t + 1], g_wfix[3 * t + 2]};
+            for (int s = 1; s < hsets; s++) {
+                const int64_t u = t + (int64_t)s * nbt;
+                const unsigned long long d[3] = {g_wfix[3 * u], g_wfix[3 * u + 1],
+                                                 g_wfix[3 * u + 2]};
+                fixed_add(f, d);
+            }
             if (autocorr) {
                 f[2] = (f[2] << 1) | (f[1] >> 63);
                 f[1] = (f[1] << 1) | (f[0] >> 63);
@@ -1657,7 +1688,7 @@ __global__ void k_finalize(int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
         if (out_wsum)
             out_wsum[t] = w;
         if (out_ravg) {
-            const double r = autocorr ? 2.0 * g_rhist[t] : g_rhist[t];
+            const double r = autocorr ? 2.0 * rs : rs;
             out_ravg[t] = w != 0.0 ? r / w : 0.0;
         }
     }
@@ -1760,14 +1791,14 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
-                           double *out_ravg)
+                           double *out_ravg, int32_t hsets)
 {
     const int64_t total = (int64_t)ncat * nbt;
     int64_t g = (total + 255) / 256;
     g = g < 1 ? 1 : (g > 4096 ? 4096 : g);
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)g), dim3(256), 0, s, ncat, nbt, autocorr,
                        e0_zero, cats, g_hist, g_whist, g_rhist, wsq, g_wfix, wsq_fix, wfx,
-                       out_counts, out_wsum, out_ravg);
+                       out_counts, out_wsum, out_ravg, hsets);
     return hipGetLastError();
 }
 
