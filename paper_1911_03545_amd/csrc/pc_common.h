@@ -109,6 +109,9 @@ struct pc_grid {
     double dec_lo;
     double inv_hs;
     double sky_reach;   // angular reach with its margins (radians)
+    // expanded binary64 r sweep: receives c^2 |b|^2 of every sorted point (or
+    // NULL), c = fscale; the float32 coordinates are then not written
+    double *q64;
     const pc_band *bands;
 };
 

@@ -565,6 +565,15 @@ __device__ __forceinline__ void store_sorted(const pc_grid &g, const double4 &r,
                                              double *xd, double *yd, double *zd, double *wd,
                                              float4 *P)
 {
+    xd[d] = r.x;
+    yd[d] = r.y;
+    zd[d] = r.z;
+    if (wd)
+        wd[d] = r.w;
+    if (g.q64) {
+        g.q64[d] = ((r.x * r.x + r.y * r.y) + r.z * r.z) * (g.fscale * g.fscale);
+        return;
+    }
     float fx, fy, fz;
     if (g.xy_local) {
         int ix, iy;
@@ -590,11 +599,6 @@ __device__ __forceinline__ void store_sorted(const pc_grid &g, const double4 &r,
         Y[d] = fy;
     }
     Z[d] = fz;
-    xd[d] = r.x;
-    yd[d] = r.y;
-    zd[d] = r.z;
-    if (wd)
-        wd[d] = r.w;
 }
 
 // ---- blocks of up to 64 points per column --------------------------------
@@ -932,10 +936,12 @@ __device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b
     }
 }
 
-// Work items.  Thread t makes visit t % visits of block t / visits (a block's
-// items stay together in the list: the sweep keeps a block's points across
-// its items, and ran 5% slower on a list by visits): it counts the items of
-// its segments, the workgroup sums them, and the items go to
+// Work items.  A thread makes one visit of one block, eight blocks of a visit
+// side by side (their items, which share most of their j points, follow each
+// other: 2380 -> 2270 us for DR(theta)'s sweep; the visits of a block must stay
+// close in the list too, which a list by visits of 256 blocks lost, 587 -> 617
+// us for 10^6 points): it counts the items of its segments, the workgroup sums
+// them, and the items go to
 //   MODE 0: nowhere; the workgroup's total to wcnt (ordered lists, first pass)
 //   MODE 1: the places after the scanned totals woff (second pass; the last
 //           workgroup leaves the list's length in n_items)
@@ -952,9 +958,10 @@ __global__ __launch_bounds__(kItemThreads) void k_items(
     int32_t *icell, int32_t *n_items, unsigned long long *cand, int32_t *n_blocks)
 {
     const unsigned long long t0 = (unsigned long long)blockIdx.x * kItemThreads;
-    const unsigned tr = (unsigned)(t0 % (unsigned)visits) + threadIdx.x;
-    const int bi = (int)(t0 / (unsigned)visits) + (int)(tr / (unsigned)visits);
-    const int visit = (int)(tr % (unsigned)visits);
+    const unsigned gv = 8u * (unsigned)visits;
+    const unsigned tr = (unsigned)(t0 % gv) + threadIdx.x;
+    const int bi = 8 * ((int)(t0 / gv) + (int)(tr / gv)) + (int)(tr % 8u);
+    const int visit = (int)(tr % gv / 8u);
     const int wg = (int)blockIdx.x;
     pc_block b;
     b.ni = 0;
@@ -1301,7 +1308,7 @@ hipError_t launch_block_emit(hipStream_t s, int32_t ncol, int32_t nz, const int3
 
 int64_t item_workgroups(int64_t nblocks, const pc_grid &g, int autocorr)
 {
-    const int64_t t = nblocks * segment_visits(g.nband > 0, g.xyk, autocorr != 0);
+    const int64_t t = (nblocks + 7) / 8 * 8 * segment_visits(g.nband > 0, g.xyk, autocorr != 0);
     return std::max<int64_t>((t + kItemThreads - 1) / kItemThreads, 1);
 }
 

@@ -61,7 +61,11 @@ struct SweepArgs {
     // float32 DD(r) and DD(rp, pi) of 3-D grids: x and y expanded as |a|^2 +
     // |b|^2 - 2 a.b, with P2 = (x, y, z, |b|^2) of every sorted point of side
     // 2 in float32 (z: the rp/pi path's fixed-point bits)
+    // (binary64 DD(r): xy_exp says that all three axes are expanded in binary64,
+    // with q2 = c^2 |b|^2 of every sorted point of side 2 and c2 = c^2)
     int32_t xy_exp;
+    const double *q2;
+    double c2;
     const float4 *P2;
     // the expanded bands hold the magnitude term xy_M (scaled coordinates)
     // times xy_K; a pair whose own magnitude term m is smaller may narrow
@@ -197,7 +201,7 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
 // resident sweep workgroups per CU for a dynamic LDS size
 // waves per sweep workgroup
 int sweep_waves();
-// (exp: the float32 r sweep with x and y expanded)
+// (exp: the sweep with expanded squares)
 hipError_t sweep_occupancy(int metric, bool fp32, int wmode, bool t16, bool unc, bool priv,
                            bool exp, int lds_bytes, int *per_cu);
 // device address and size of the fixed scratch of the no-allocation entry

@@ -525,11 +525,41 @@ int fp32_scale(int metric, const double *edges, int nb, double coord_scale, bool
     return CF_OK;
 }
 
+// The expanded binary64 r sweep computes c^2 s as c^2 |a|^2 + c^2 |b|^2 + sum
+// (-2 c^2 a_k) b_k in binary64.  Its errors, in units of u (A + B), u = 2^-53,
+// A = |a|^2, B = |b|^2: the shifted coordinate a = fl(x + D) 4, the factors
+// -2 c^2 a_k 1, the two squares 4, their sum 1, three fused multiply-adds 6
+// (partial sums at most 2 (A + B)), together 16; the definition's own
+// roundings, at most 6 u s, 12 more.  d64 = 32 u (A + B) bounds the distance
+// between the two; a pair within d64 of an edge is decided by the definition.
+// Taken while d64 is below 2^-12 of the smallest nonzero edge squared, so that
+// such pairs stay rare, and below 2^-18 of the largest, so that a value
+// rounded below zero still has the key 0.
+double expand64(const double *edges, int nb, double mag, double *c)
+{
+    if (rounding_key(nb, false) && mag > 0.0 && std::isfinite(mag)) {
+        const double d = 32.0 * 0x1p-53 * mag;
+        const double top = edges[nb] * edges[nb];
+        double emin = top;
+        for (int k = 0; k <= nb; k++)
+            if (edges[k] > 0.0)
+                emin = std::min(emin, edges[k] * edges[k]);
+        const double cc = std::sqrt(key_top(nb, false) * (1.0 - 0x1p-16) / (top + d));
+        // (a normal float32 for every band, no overflow of the scaled squares)
+        if (d <= 0x1p-12 * emin && d <= 0x1p-18 * top && std::isfinite(cc) && cc > 0.0 &&
+            mag * cc * cc < 0x1p100 && emin * cc * cc > 0x1p-100) {
+            *c = cc;
+            return d;
+        }
+    }
+    return 0.0;
+}
+
 int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
                int npi, double coord_scale, const double *axis_eps, double fscale, bool priv,
-               double xy_mag, HostBins *out)
+               double xy_mag, HostBins *out, double d64)
 {
-    if (!fp32)
+    if (!fp32 && !(d64 > 0.0))
         fscale = 1.0;
     if (nb < 1 || nb + 1 > PC_MAX_EDGES)
         return CF_EINVAL;
@@ -555,6 +585,20 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
                              lo.data(), hi.data(), axis_eps ? xy_mag : 0.0);
         if (rc)
             return rc;
+    } else if (d64 > 0.0) {
+        const double c2 = fscale * fscale;
+        for (int k = 0; k < ne; k++) {
+            if (E[k] == 0.0) {
+                lo[k] = hi[k] = -1.0f;
+            } else {
+                lo[k] = float_down((E[k] - d64) * c2 * (1.0 - 0x1p-50));
+                hi[k] = float_up((E[k] + d64) * c2 * (1.0 + 0x1p-50));
+            }
+        }
+        for (int k = ne - 2; k >= 0; k--)
+            lo[k] = std::min(lo[k], lo[k + 1]);
+        for (int k = 1; k < ne; k++)
+            hi[k] = std::max(hi[k], hi[k - 1]);
     } else {
         fp64_bands(E.data(), ne, lo.data(), hi.data());
     }
@@ -608,8 +652,9 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
     uint32_t base = 0, tbl_n = 0;
     const bool wide = nb > PC_TBL8_MAX_BINS;
     const bool rppi = metric == PC_METRIC_RPPI;
-    const bool pk = fp32 && rounding_key(nb, priv);
-    if (fp32) {
+    const bool keyed = fp32 || d64 > 0.0;
+    const bool pk = keyed && rounding_key(nb, priv);
+    if (keyed) {
         tbl_n = pk ? (uint32_t)PC_TBL_PK_CELLS : (uint32_t)table_cells(nb, priv);
         if (!((double)hi[nb] < key_top(nb, priv)))
             return CF_EINVAL;
@@ -657,7 +702,7 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
     h.pimax = (metric == PC_METRIC_RPPI) ? pimax : 0.0;
     h.row_w = rppi ? npi + 2 : 1;
     h.col0 = rppi ? 1 : 0;
-    h.tbl_linear = fp32 ? (pk ? 2 : 1) : 0;
+    h.tbl_linear = keyed ? (pk ? 2 : 1) : 0;
     h.tbl_out_zero = rppi ? 1 : 0;
     h.tbl_ordered = ordered ? 1 : 0;
 

@@ -48,8 +48,14 @@ int fp32_scale(int metric, const double *edges, int nb, double coord_scale, bool
                const double *axis_eps, double xy_mag, double *c);
 // axis_eps (optional, x y z): per-axis rounding bounds (else box-frame 6 u S);
 // fscale: the float32 coordinate scale (bands are moved into it)
+// d64 > 0 (binary64 r only): bands and table of the expanded binary64 sweep,
+// whose squared separations are within d64 of the definition's
 int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax, int npi,
                double coord_scale, const double *axis_eps, double fscale, bool priv,
-               double xy_mag, HostBins *out);
+               double xy_mag, HostBins *out, double d64 = 0.0);
+// Bound d64 of the expanded binary64 r sweep for coordinates of squared
+// magnitudes |a|^2 + |b|^2 <= mag, and its coordinate scale; 0 where the form
+// does not pay (see the definition)
+double expand64(const double *edges, int nb, double mag, double *c);
 
 }  // namespace pc
