@@ -1136,6 +1136,16 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         }
         d64 = pc::expand64(lin.data(), nb, mag, &fscale);
     }
+    // On-sky pairs: formed in fewer operations where the observer's distance
+    // and the bins allow it (the mean separation takes the root of rp^2 and
+    // keeps the definition's order)
+    double mk_ds = 0.0, mk_dpi = 0.0, mk_m2 = 0.0;
+    if (sky && !want_ravg) {
+        for (int a = 0; a < 3; a++)
+            mk_m2 += std::max(lo[a] * lo[a], hi[a] * hi[a]);
+        if (!pc::mocks_bounds(lin.data(), nb, pimax, npi, mk_m2, &mk_ds, &mk_dpi))
+            mk_ds = 0.0;
+    }
     g.fscale = fscale;
     record(c, timing, 1);
 
@@ -1246,7 +1256,8 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     pc::HostBins hb;
     // on-sky pairs bin (rp, pi) like the Cartesian statistic
     rc = pc::build_bins(sky ? PC_METRIC_RPPI : metric, fp32, lin.data(), nb, pimax, npi, scale,
-                        g.xy_local ? axis_eps : nullptr, fscale, priv, xy_mag, &hb, d64);
+                        g.xy_local ? axis_eps : nullptr, fscale, priv, xy_mag, &hb,
+                        sky ? mk_ds : d64);
     if (rc)
         return fail(c, (cf_status)rc, "bin description failed");
     if (g.zq_shift > 0) {
@@ -1397,7 +1408,16 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     a.rq_count = (unsigned *)(misc(c) + M_RQCOUNT);
     a.flush_count = (unsigned *)(misc(c) + M_FLUSH);
     a.xy_local = g.xy_local;
-    const bool exp_form = xy_mag > 0.0 || d64 > 0.0;
+    bool exp_form = xy_mag > 0.0 || d64 > 0.0;
+    if (mk_ds > 0.0) {
+        const double tau = (double)hb.hdr.pi_tau + mk_dpi * npi / pimax;
+        exp_form = tau < 0.25;
+        a.mk_tau = (float)(tau * (1.0 + 0x1p-20));
+        a.mk_lim = (hb.hdr.E_top + pimax * pimax) * (1.0 + 0x1p-30);
+        a.mk_ll = mk_m2 / 16.0;
+        a.mk_E = hb.hdr.E_top + mk_ds;
+        a.mk_pi = pimax + mk_dpi;
+    }
     a.xy_exp = exp_form ? 1 : 0;
     a.q2 = d64 > 0.0 ? dptr<double>(c, autocorr ? B_Q1 : B_Q2) : nullptr;
     a.c2 = g.fscale * g.fscale;

@@ -63,7 +63,13 @@ struct SweepArgs {
     // 2 in float32 (z: the rp/pi path's fixed-point bits)
     // (binary64 DD(r): xy_exp says that all three axes are expanded in binary64,
     // with q2 = c^2 |b|^2 of every sorted point of side 2 and c2 = c^2)
+    // (on-sky: xy_exp says that pairs are first formed with the bounds below)
     int32_t xy_exp;
+    // on-sky sweep: a pair whose s.s is at most mk_lim is formed in fewer
+    // operations, off by at most mk_ds in rp^2 and mk_dpi in pi while |L|^2 is at
+    // least mk_ll; mk_tau is the margin of its fast pi bin
+    double mk_lim, mk_ll, mk_E, mk_pi;
+    float mk_tau;
     const double *q2;
     double c2;
     const float4 *P2;

@@ -525,6 +525,31 @@ int fp32_scale(int metric, const double *edges, int nb, double coord_scale, bool
     return CF_OK;
 }
 
+// The on-sky sweep forms sl = s.L as 2 s.v_i - s.s and ll = |L|^2 as 4 |v_i|^2 -
+// 2 s.v_i - sl (s = v_i - v_j, L = v_i + v_j = 2 v_i - s), the reciprocal root
+// of ll by one Newton step from v_rsq_f64 (documented to 2^29 ulp, so 2^-45
+// after the step), pi = |sl| / |L| and rp^2 = s.s - pi^2.  With R^2 the largest
+// s.s that can be in range, M the largest distance from the observer and ll >=
+// M^2 / 16, in units of u = 2^-53: sl is off by at most 32 R M (both forms'
+// roundings), so pi by 128 R; ll by 40 M^2, 640 relative, so pi by 320 R; the
+// root's 2^-45 is 256 R.  2^-38 R = 2^15 u R is far above their sum, and 2^-36
+// R^2 above the error of rp^2 (2 R times that, and 8 u R^2).  Pairs within
+// these of an edge, or with a smaller ll, are decided by the definition.
+bool mocks_bounds(const double *edges, int nb, double pimax, int npi, double m2, double *ds,
+                  double *dpi)
+{
+    const double R2 = (edges[nb] * edges[nb] + pimax * pimax) * (1.0 + 0x1p-29);
+    double emin = edges[nb] * edges[nb];
+    for (int k = 0; k <= nb; k++)
+        if (edges[k] > 0.0)
+            emin = std::min(emin, edges[k] * edges[k]);
+    *ds = 0x1p-36 * R2;
+    *dpi = 0x1p-38 * std::sqrt(R2);
+    // worth it while few pairs are undecided; and with room for every square
+    return *ds <= 0x1p-10 * emin && *dpi * npi <= 0x1p-10 * pimax && m2 >= R2 * 0x1p-20 &&
+           m2 < 0x1p200 && m2 > 0x1p-200 && R2 > 0x1p-200;
+}
+
 // The expanded binary64 r sweep computes c^2 s as c^2 |a|^2 + c^2 |b|^2 + sum
 // (-2 c^2 a_k) b_k in binary64.  Its errors, in units of u (A + B), u = 2^-53,
 // A = |a|^2, B = |b|^2: the shifted coordinate a = fl(x + D) 4, the factors
@@ -559,7 +584,8 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
                int npi, double coord_scale, const double *axis_eps, double fscale, bool priv,
                double xy_mag, HostBins *out, double d64)
 {
-    if (!fp32 && !(d64 > 0.0))
+    const bool keyed = fp32 || (d64 > 0.0 && metric == PC_METRIC_R);
+    if (!keyed)
         fscale = 1.0;
     if (nb < 1 || nb + 1 > PC_MAX_EDGES)
         return CF_EINVAL;
@@ -585,7 +611,7 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
                              lo.data(), hi.data(), axis_eps ? xy_mag : 0.0);
         if (rc)
             return rc;
-    } else if (d64 > 0.0) {
+    } else if (keyed) {
         const double c2 = fscale * fscale;
         for (int k = 0; k < ne; k++) {
             if (E[k] == 0.0) {
@@ -601,6 +627,13 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
             hi[k] = std::max(hi[k], hi[k - 1]);
     } else {
         fp64_bands(E.data(), ne, lo.data(), hi.data());
+        for (int k = 0; d64 > 0.0 && k < ne; k++) {
+            // (a pair near a zero first edge: rp^2 is clamped at zero)
+            if (E[k] > 0.0) {
+                lo[k] = float_down(std::max(E[k] - d64, 0.0));
+                hi[k] = float_up(E[k] + d64);
+            }
+        }
     }
     const int nq = (metric == PC_METRIC_RPPI) ? npi + 1 : 1;
     std::vector<double> q(nq, 0.0);
@@ -652,7 +685,6 @@ int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax,
     uint32_t base = 0, tbl_n = 0;
     const bool wide = nb > PC_TBL8_MAX_BINS;
     const bool rppi = metric == PC_METRIC_RPPI;
-    const bool keyed = fp32 || d64 > 0.0;
     const bool pk = keyed && rounding_key(nb, priv);
     if (keyed) {
         tbl_n = pk ? (uint32_t)PC_TBL_PK_CELLS : (uint32_t)table_cells(nb, priv);

@@ -48,11 +48,16 @@ int fp32_scale(int metric, const double *edges, int nb, double coord_scale, bool
                const double *axis_eps, double xy_mag, double *c);
 // axis_eps (optional, x y z): per-axis rounding bounds (else box-frame 6 u S);
 // fscale: the float32 coordinate scale (bands are moved into it)
-// d64 > 0 (binary64 r only): bands and table of the expanded binary64 sweep,
-// whose squared separations are within d64 of the definition's
+// d64 > 0 (binary64 only): the sweep's squared separations are within d64 of
+// the definition's; r: bands and table of the expanded sweep (keyed like the
+// float32 ones); on-sky rp: bands widened by d64
 int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax, int npi,
                double coord_scale, const double *axis_eps, double fscale, bool priv,
                double xy_mag, HostBins *out, double d64 = 0.0);
+// On-sky pairs formed from 2 s.v_i: bounds of the error in rp^2 and pi for
+// points within sqrt(m2) of the observer (false: the form is not taken)
+bool mocks_bounds(const double *edges, int nb, double pimax, int npi, double m2, double *ds,
+                  double *dpi);
 // Bound d64 of the expanded binary64 r sweep for coordinates of squared
 // magnitudes |a|^2 + |b|^2 <= mag, and its coordinate scale; 0 where the form
 // does not pay (see the definition)
