@@ -143,7 +143,9 @@ typedef struct cf_options {
                                    gives.  Other statistics need 0.            */
     int32_t xy_refine;          /* 3-D grids: columns at least reach/k wide in
                                    x and y (section "Sub-dividing the cells"),
-                                   k in 1..4 (0: 1); a block then pairs with
+                                   k in 1..4 (0: chosen from the points' mean
+                                   density and the reach; 1 for batches and
+                                   angular counts); a block then pairs with
                                    the (2k+1)^2 columns around its own, each
                                    over a z window narrowed by the columns'
                                    transverse distance when the reach is a

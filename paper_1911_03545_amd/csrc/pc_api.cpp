@@ -876,8 +876,6 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         return fail(c, CF_EINVAL, "flush_pairs must be >= 0");
     if (opt.xy_refine < 0 || opt.xy_refine > PC_MAX_XYK)
         return fail(c, CF_EINVAL, "xy_refine must be in [0, %d]", PC_MAX_XYK);
-    if (opt.xy_refine == 0)
-        opt.xy_refine = 1;
     if (opt.slices_per_reach <= 0)
         opt.slices_per_reach = 32;
 
@@ -1033,6 +1031,16 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     }
 
     // ---- plan ------------------------------------------------------------
+    if (opt.xy_refine == 0)
+        opt.xy_refine = (theta || ncat > 1)
+                            ? 1
+                            : pc::choose_refine(lo, hi, boxsize, reach_xy, reach_z,
+                                                metric != PC_METRIC_RPPI, (double)n1, (double)n2,
+                                                autocorr,
+                                                (sky || metric == PC_METRIC_RPPI ? 2000.0
+                                                 : weighted                      ? 4300.0
+                                                                                 : 2500.0) *
+                                                    (prec == CF_PREC_FP64 || sky ? 0.5 : 1.0));
     pc_grid g;
     // r, angular chords and on-sky pairs are bounded by a 3-D ball
     int rc = pc::plan_grid(lo, hi, boxsize, reach_xy, reach_z, opt.slices_per_reach, &g,

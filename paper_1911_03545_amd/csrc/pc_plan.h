@@ -20,6 +20,12 @@ struct HostBins {
 int plan_grid(const double lo[3], const double hi[3], double boxsize, double reach_xy,
               double reach_z, int slices_per_reach, pc_grid *g, int xy_refine = 1,
               bool zball = false);
+// x/y refinement for which the sweep's expected work is least (points of the
+// two sides spread evenly over the domain); item_cost: pairs that a work item
+// costs beyond its own
+int choose_refine(const double lo[3], const double hi[3], double boxsize, double reach_xy,
+                  double reach_z, bool zball, double n1, double n2, bool autocorr,
+                  double item_cost);
 // angular grid of unit vectors (overrides n, ncell, zreach and the slice
 // fields of a grid planned on the vectors' bounding box)
 int plan_sky_grid(double chord_reach, double zlo, double zhi, int slices, int ra_refine,
