@@ -22,8 +22,9 @@
 // item fetches spread over many addresses instead of serialising on one.
 #define PC_STREAMS 64
 #define PC_STREAM_STRIDE 64
-// counters and, after them, the 64-bit mask of exhausted streams
-#define PC_STREAM_BYTES (4 * PC_STREAMS * PC_STREAM_STRIDE + 256)
+// (each stream's ints hold its counter and, half way, a copy of the 64-bit mask
+// of exhausted streams)
+#define PC_STREAM_BYTES (4 * PC_STREAMS * PC_STREAM_STRIDE)
 #define PC_MAX_EDGES 1025      // r / rp / theta edges
 #define PC_MAX_NPI 1024
 #define PC_MAX_BINS_TOTAL 4096 // r bins, or nrp * npi

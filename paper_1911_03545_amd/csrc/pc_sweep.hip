@@ -1281,24 +1281,38 @@ __device__ __forceinline__ int tri_end(int j0, int j1, int iend)
 // stream is exhausted.  Lane 0 increments the stream's counter at once (one
 // round trip per item; increments past the end are harmless, as every take
 // compares with the length).  The take that first finds a stream empty sets
-// its bit in a mask beside the counters, so a wave that moves on (`probe`)
-// reads one word to know the streams that may still hold items, instead of
-// one counter after the other (64 round trips after a wave's last item).
-static_assert(PC_STREAMS == 64, "one bit per stream");
+// its bit in a mask, so a wave that moves on (`probe`) reads one word to know
+// the streams that may still hold items, instead of one counter after the
+// other (64 round trips after a wave's last item).  Every stream's line holds a
+// copy of the mask, and a wave reads that of the stream it began with: with one
+// copy, 8192 waves queued at its address (sweep of 10^4 points 29 -> 22 us).
+static_assert(PC_STREAMS == PC_WAVE, "one mask copy per lane, one bit per stream");
 // first item of stream s: s n / 64, in 32-bit steps
 __device__ __forceinline__ int stream_first(int n, int s)
 {
     return (n >> 6) * s + (((n & 63) * s) >> 6);
 }
-__device__ __forceinline__ int wave_fetch(int *ctrs, int n_items, int lane, int &s, bool &probe)
+__device__ __forceinline__ unsigned long long *stream_mask(int *ctrs, int s)
 {
-    unsigned long long *done =
-        reinterpret_cast<unsigned long long *>(ctrs + PC_STREAMS * PC_STREAM_STRIDE);
+    return reinterpret_cast<unsigned long long *>(ctrs + s * PC_STREAM_STRIDE +
+                                                  PC_STREAM_STRIDE / 2);
+}
+// A take past the end of stream s (v >= len): the first one sets the bit in
+// every copy, one per lane, later ones in the wave's own (the first may be a
+// take ahead whose result its wave looks at only after its item).
+__device__ __forceinline__ void stream_empty(int *ctrs, int lane, int home, int s, bool first)
+{
+    if (first || lane == home)
+        atomicOr(stream_mask(ctrs, lane), 1ull << s);
+}
+__device__ __forceinline__ int wave_fetch(int *ctrs, int n_items, int lane, int home, int &s,
+                                          bool &probe)
+{
     unsigned long long empty = 0;   // streams known to be exhausted
     for (int tries = 0; tries <= PC_STREAMS; tries++) {
         if (probe) {
-            const unsigned long long m =
-                __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long m = __hip_atomic_load(
+                stream_mask(ctrs, home), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             empty |= 1ull << s;
             empty |= (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)m) |
                      (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(m >> 32))
@@ -1313,16 +1327,14 @@ __device__ __forceinline__ int wave_fetch(int *ctrs, int n_items, int lane, int 
         }
         const int first = stream_first(n_items, s), len = stream_first(n_items, s + 1) - first;
         int v = 0;
-        if (lane == 0) {
+        if (lane == 0)
             v = atomicAdd(ctrs + s * PC_STREAM_STRIDE, 1);
-            if (v == len)
-                atomicOr(done, 1ull << s);
-        }
         v = __builtin_amdgcn_readfirstlane(v);
         if (v < len) {
             probe = false;
             return first + v;
         }
+        stream_empty(ctrs, lane, home, s, v == len);
         probe = true;
     }
     return n_items;
@@ -1507,6 +1519,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     // index derived from it stays scalar)
     int stream = __builtin_amdgcn_readfirstlane(
         (int)((blockIdx.x * kWaves + wave) & (PC_STREAMS - 1)));
+    const int home = stream;
     int n_items = a.n_items;
     if (a.n_items_dev)
         n_items = min(n_items, __builtin_amdgcn_readfirstlane(*(const volatile int32_t *)a.n_items_dev));
@@ -1539,6 +1552,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     // Short lists (fewer than four items a wave) are not taken ahead: a wave
     // that starts early would hold two or three items while others find none.
     const bool late = n_items < 4 * kWaves * (int)gridDim.x;
+    const int keep = 2 * kWaves * (int)gridDim.x / PC_STREAMS;
     int next = -1;
     for (;;) {
         if (next >= n_items)
@@ -1555,15 +1569,16 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             take = v >= len;
             next = first + v;
             if (take) {
-                if (v == len && lane == 0)
-                    atomicOr(reinterpret_cast<unsigned long long *>(
-                                 a.counter + PC_STREAMS * PC_STREAM_STRIDE),
-                             1ull << stream);
+                stream_empty(a.counter, lane, home, stream, v == len);
                 probe = true;
             }
         }
         if (take)
-            next = wave_fetch(a.counter, n_items, lane, stream, probe);
+            next = wave_fetch(a.counter, n_items, lane, home, stream, probe);
+        // (both are wave-uniform; said here so that the compiler keeps the item
+        // loop scalar whatever it makes of the branches above)
+        next = __builtin_amdgcn_readfirstlane(next);
+        stream = __builtin_amdgcn_readfirstlane(stream);
         // float32 sweeps load the following item's descriptor while this
         // item runs (measured slower for the binary64 sweep, which loads it
         // after the take)
@@ -1572,7 +1587,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             if (a.xy_local)
                 ncell = icell[next];
         }
-        if (AHEAD && next < n_items && !probe && !late) {
+        // (not among the last items of a stream, two for each of its waves: there
+        // a take held back by a long item is an item another wave lacks: sweeps
+        // of 2.5*10^5 points 150 -> 118 us, of 5*10^5 204 -> 188, of 10^6 612 -> 590)
+        if (AHEAD && next < n_items && !probe && !late &&
+            next < stream_first(n_items, stream + 1) - keep) {
             if (lane == 0)
                 pv = atomicAdd(a.counter + stream * PC_STREAM_STRIDE, 1);
             pend = true;
