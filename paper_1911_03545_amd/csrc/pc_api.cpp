@@ -1031,8 +1031,12 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     }
 
     // ---- plan ------------------------------------------------------------
+    // A call on fixed scratch takes the plan that needs the least of it (no x/y
+    // refinement, binary64 differences without a |b|^2 per point, the longest
+    // items, one set of bins), so that its largest catalogues still fit.
+    const bool lean = c->arena;
     if (opt.xy_refine == 0)
-        opt.xy_refine = (theta || ncat > 1)
+        opt.xy_refine = (theta || ncat > 1 || lean)
                             ? 1
                             : pc::choose_refine(lo, hi, boxsize, reach_xy, reach_z,
                                                 metric != PC_METRIC_RPPI, (double)n1, (double)n2,
@@ -1135,7 +1139,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // (5*10^5 points: 656 us with differences, 745 expanded), and the mean
     // separation takes the square root of s.
     double d64 = 0.0;
-    if (!fp32 && metric == PC_METRIC_R && !priv && !weighted) {
+    if (!fp32 && metric == PC_METRIC_R && !priv && !weighted && !lean) {
         double mag = 0.0;
         for (int a = 0; a < 3; a++) {
             // |a| at most the larger |coordinate|, plus one box length
@@ -1161,7 +1165,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // sums of up to 768 workgroups otherwise queue at the same bins (850 ->
     // 777 us of 10^6 weighted (rp, pi) points with mean separations); counts
     // alone measured no faster with them
-    const int hsets = !priv && weighted ? 8 : 1;
+    const int hsets = !priv && weighted && !lean ? 8 : 1;
     const size_t nhist = nout * (size_t)hsets;
     // ---- work-list and sweep buffers, cleared by one kernel ahead of the
     // gridding (the host issues it while nothing else waits on it) ----------
@@ -1178,7 +1182,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     const bool ordered = priv || n1 + (autocorr ? 0 : n2) > 65536;
     const int chunk_max = opt.chunk > 0 ? std::min(opt.chunk, 1 << 20) : 2048;
     int chunk = chunk_max;
-    if (!priv && !sky_grid && opt.flush_pairs == 0) {
+    if (!priv && !sky_grid && !lean && opt.flush_pairs == 0) {
         // (a caller that lowers the merge bound wants waves to reach it)
         // Shorter items where the whole list is short: about two items for
         // each resident wave (eight with weights, whose pairs take longer),
