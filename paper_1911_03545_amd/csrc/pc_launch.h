@@ -111,7 +111,10 @@ hipError_t launch_radec(hipStream_t s, int64_t n, const void *ra, const void *de
                         unsigned *flags);
 hipError_t launch_minmax(hipStream_t s, int64_t n, const void *x, const void *y,
                          const void *z, int f32, double *part, int nparts, unsigned *flags);
-hipError_t launch_minmax_final(hipStream_t s, const double *part, int nparts, double *out6);
+hipError_t launch_minmax_final(hipStream_t s, const double *part, int nparts,
+                               const unsigned *flags, double *out6, unsigned *flags_out);
+hipError_t launch_put_cats(hipStream_t s, const pc_cat *cat1, pc_cat *dst1, const pc_cat *cat2,
+                           pc_cat *dst2);
 // cell and in-cell rank of every point of a side's catalogues, plus a
 // 32-byte (x, y, z, w) record per point in input order (rec: ntot records)
 hipError_t launch_cell_index(hipStream_t s, int ncat, const pc_cat *cats, int64_t ntot,
@@ -203,7 +206,8 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
-                           double *out_ravg, int32_t hsets);
+                           double *out_ravg, int32_t hsets, const void *misc, void *misc_out,
+                           size_t misc_bytes);
 // resident sweep workgroups per CU for a dynamic LDS size
 // waves per sweep workgroup
 int sweep_waves();

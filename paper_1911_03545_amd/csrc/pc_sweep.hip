@@ -1887,8 +1887,13 @@ __global__ void k_finalize(int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum, double *out_ravg,
-                           int32_t hsets)
+                           int32_t hsets, const unsigned *misc, unsigned *misc_out,
+                           int32_t misc_words)
 {
+    // (every kernel that writes the flags and counters ran before this one)
+    if (blockIdx.x == 0)
+        for (int k = threadIdx.x; k < misc_words; k += blockDim.x)
+            misc_out[k] = misc[k];
     const int64_t total = (int64_t)ncat * nbt;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
          t += (int64_t)gridDim.x * blockDim.x) {
@@ -2051,14 +2056,17 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                            const unsigned long long *g_wfix,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
-                           double *out_ravg, int32_t hsets)
+                           double *out_ravg, int32_t hsets, const void *misc, void *misc_out,
+                           size_t misc_bytes)
 {
     const int64_t total = (int64_t)ncat * nbt;
     int64_t g = (total + 255) / 256;
     g = g < 1 ? 1 : (g > 4096 ? 4096 : g);
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)g), dim3(256), 0, s, ncat, nbt, autocorr,
                        e0_zero, cats, g_hist, g_whist, g_rhist, wsq, g_wfix, wsq_fix, wfx,
-                       out_counts, out_wsum, out_ravg, hsets);
+                       out_counts, out_wsum, out_ravg, hsets,
+                       static_cast<const unsigned *>(misc), static_cast<unsigned *>(misc_out),
+                       (int32_t)(misc_bytes / sizeof(unsigned)));
     return hipGetLastError();
 }
 
