@@ -207,8 +207,10 @@ typedef struct cf_options {
                                    against the band narrowed by its own
                                    magnitudes, then rechecked in binary64);
                                    0 (default): 2 when that bound widens the
-                                   band of the smallest nonzero edge by at
-                                   most an eighth of its value, else 1.  Other
+                                   band of the smallest nonzero squared edge
+                                   by at most an eighth of its value (DD(r)
+                                   and chords of up to 125 bins: 4 times its
+                                   value), else 1.  Other
                                    statistics and the binary64 mode ignore
                                    it.  cf_stats.separation_form reports the
                                    form used.                                  */

@@ -1112,10 +1112,16 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // Float32 DD(r) (and chords) and DD(rp, pi) of 3-D grids without the
     // mean separation: x and y expanded as |a|^2 + |b|^2 - 2 a.b, one
     // instruction fewer per pair.  By default only while its absolute
-    // rounding term widens the band of the smallest nonzero edge by at most
-    // an eighth of that edge (the sweep narrows each pair's band by its own
-    // magnitudes before a binary64 recheck, which keeps the rechecks of the
-    // crowded small rp edges in check).  (The float32 mean separation takes
+    // rounding term widens the band of the smallest nonzero edge squared by at
+    // most an eighth of it for (rp, pi), whose crowded small rp edges many pairs
+    // meet (1.7 times: 1260 us with differences, 1325 expanded, 7 times the
+    // rechecks), and by at most 4 times for r, where few pairs lie that near and
+    // the sweep narrows each pair's band by its own magnitudes before a binary64
+    // recheck: 0.43 times, 4*10^6 points, reach 50: sweep 2968 us with
+    // differences, 2665 expanded, with weights 6100 and 5310; 1.7 times, 10^6
+    // points, reach 100: 1508 and 1464; still faster at 12 times (1490 and 1416).
+    // (Tables of 16 bits, whose cells are linear, keep the eighth, as do
+    // calls on fixed scratch, which the form takes 16 bytes a point of.)  (The float32 mean separation takes
     // the square root of s and keeps the differences.)
     double xy_mag = 0.0;
     if (fp32 && g.xy_local && (metric == PC_METRIC_R || metric == PC_METRIC_RPPI) && !sky &&
@@ -1127,7 +1133,9 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         for (int k = 0; k <= nb; k++)
             if (lin[k] > 0.0)
                 emin = std::min(emin, lin[k] * lin[k]);
-        if (opt.separation_form == 2 || 1.25 * 0x1p-24 * mag <= 0.125 * emin)
+        const double most =
+            metric == PC_METRIC_R && nb <= PC_TBL8_MAX_BINS && !lean ? 4.0 : 0.125;
+        if (opt.separation_form == 2 || 1.25 * 0x1p-24 * mag <= most * emin)
             xy_mag = mag;
     }
     // batches: private per-wave histograms, flushed per catalogue
