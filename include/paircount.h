@@ -210,7 +210,11 @@ typedef struct cf_options {
                                    band of the smallest nonzero squared edge
                                    by at most an eighth of its value (DD(r)
                                    and chords of up to 125 bins: 4 times its
-                                   value), else 1.  Other
+                                   value), else 1.  With up to 125 bins a
+                                   call on one or two catalogues takes 1,
+                                   whatever is asked, where the bound exceeds
+                                   2^-17 of the largest squared edge (columns
+                                   beyond twice the reach).  Other
                                    statistics and the binary64 mode ignore
                                    it.  cf_stats.separation_form reports the
                                    form used.                                  */

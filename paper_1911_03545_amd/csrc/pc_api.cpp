@@ -1135,7 +1135,10 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
                 emin = std::min(emin, lin[k] * lin[k]);
         const double most =
             metric == PC_METRIC_R && nb <= PC_TBL8_MAX_BINS && !lean ? 4.0 : 0.125;
-        if (opt.separation_form == 2 || 1.25 * 0x1p-24 * mag <= most * emin)
+        // (byte tables of single catalogues: the rounding key)
+        const bool keyed = ncat > 1 || nb > PC_TBL8_MAX_BINS ||
+                           pc::xy_expand_keyed(mag, lin[nb] * lin[nb]);
+        if (keyed && (opt.separation_form == 2 || 1.25 * 0x1p-24 * mag <= most * emin))
             xy_mag = mag;
     }
     // batches: private per-wave histograms, flushed per catalogue

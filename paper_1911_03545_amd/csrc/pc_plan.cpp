@@ -391,6 +391,19 @@ double xy_expand_mag(const double a_max[2], const double b_max[2], int ndim)
     return ndim == 2 ? 4.0 * A + 4.0 * B + 2.0 * P : 5.0 * B + 2.0 * A + 4.0 * P;
 }
 
+// The sum of a near pair can round below zero, by kSafety u xy_mag at most (the
+// coordinate part is of the separation's size).  The rounding key has cells of
+// top / 32767 and takes values above half a cell below zero for cell 0; lower
+// ones would fall outside its table.  Columns no wider than twice the reach
+// stay below 2^-17 top (92 reach^2 for rp); a domain of thousands of reaches has
+// wider ones (1024 columns an axis), and takes the differences.  (A clamp of the
+// sum at zero, a modifier of its last instruction, measured 0.8% of the sweep on
+// every domain.  The linear key clamps for itself.)
+bool xy_expand_keyed(double xy_mag, double top_sq)
+{
+    return kSafety * kU32 * xy_mag <= 0x1p-17 * top_sq;
+}
+
 // The bound above holds for each pair with its own magnitudes, m = 5 |b|^2
 // + 2 |a|^2 + 4 (|a_x b_x| + |a_y b_y|) (rp: 4 |a|^2 + 4 |b|^2 + 2 (|a_x b_x|
 // + |a_y b_y|)), in place of xy_mag; every band

@@ -41,6 +41,9 @@ int fp32_bands_axes(const double *edges_sq, int nedges, int ndim, const double *
 // 2): a_max = the lane's largest |x|, |y| in the j column's frame, b_max = the
 // j point's
 double xy_expand_mag(const double a_max[2], const double b_max[2], int ndim);
+// whether sums with that magnitude term stay above half a cell below zero of the
+// rounding key (byte tables of single catalogues) for the largest squared edge
+bool xy_expand_keyed(double xy_mag, double top_sq);
 // per-pair narrowing of the expanded r (ndim 3) and rp (ndim 2) bands in
 // coordinates scaled by fscale: a pair whose own magnitude term is m (scaled) may take its band
 // narrowed by K (M - m) on each side; both constants rounded down

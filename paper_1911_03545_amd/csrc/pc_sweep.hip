@@ -281,25 +281,42 @@ __device__ __forceinline__ unsigned tbl_key(float s, unsigned base, int sh, unsi
 
 // Key of the float32 path's linear table: floor(s) for s below the last
 // cell, the last cell for everything above (coordinates are scaled so that
-// the top band lies below the last cell).  s is a sum of squares, or +inf
-// for an inactive lane, never negative or NaN, so its bit pattern orders
-// like its value and an integer min clamps it in one instruction.
+// the top band lies below the last cell).  A sum of squares, or +inf
+// for an inactive lane, is never negative or NaN, so its bit pattern orders
+// like its value and an integer min clamps it in one instruction.  An expanded
+// sum (EXP) rounds to either side of zero for near pairs: one median of three
+// clamps it at both ends.
+template <bool EXP>
 __device__ __forceinline__ unsigned tbl_key_linear(float s, float kmax)
 {
-    return (unsigned)__uint_as_float(min(__float_as_uint(s), __float_as_uint(kmax)));
+    if constexpr (EXP)
+        return (unsigned)__builtin_amdgcn_fmed3f(s, 0.0f, kmax);
+    else
+        return (unsigned)__uint_as_float(min(__float_as_uint(s), __float_as_uint(kmax)));
 }
 
 // Key of the float32 path: the rounding key round(min(s, 1) * 32767) of the
-// shared-histogram sweeps' byte tables in one v_cvt_pknorm_i16_f32 (s >= 0
-// here, and the high half, the conversion of 0.0, is zero), else the linear
+// shared-histogram sweeps' byte tables in one v_cvt_pknorm_i16_f32 (s is above
+// half a cell below zero: expanded sums are taken only where xy_expand_keyed
+// says so; and the high half, the conversion of 0.0, is zero), else the linear
 // key.
-template <bool PK>
+template <bool PK, bool EXP = false>
 __device__ __forceinline__ unsigned tbl_key_f32(float s, float kmax)
 {
     if constexpr (PK)
         return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_i16(s, 0.0f));
     else
-        return tbl_key_linear(s, kmax);
+        return tbl_key_linear<EXP>(s, kmax);
+}
+
+// An expanded sum where a flagged cell compares it with the edges: in the linear
+// key's scale a near pair's can lie below -1, the empty band of a zero edge, and
+// would be taken to lie below that edge.  (The separation is not negative, so
+// raising the sum to zero keeps it within the decision bands' bound.)
+template <bool PK, bool EXP>
+__device__ __forceinline__ float slow_s(float s)
+{
+    return EXP && !PK ? fmaxf(s, 0.0f) : s;
 }
 
 // Value that the key sends to the last cell ("above every edge").
@@ -490,7 +507,7 @@ __device__ __forceinline__ void chunk_f32(const SweepArgs &a, const Lds &L, lds_
             c[k] = false;
             s[k] = kmax;
         }
-        key[k] = tbl_key_f32<PK>(s[k], kmax);
+        key[k] = tbl_key_f32<PK, EXP>(s[k], kmax);
     }
     // every lane reads (no exec-mask changes), so the CH reads stay in flight;
     // byte entries of the unconditional path are read unsigned (a flagged
@@ -519,7 +536,7 @@ __device__ __forceinline__ void chunk_f32(const SweepArgs &a, const Lds &L, lds_
 #pragma unroll
             for (int k = 0; k < CH; k++) {
                 if (U8 ? (unsigned)e[k] >= PC_TBL8_BAND : is_slow<T16>(e[k])) {
-                    int slot = slow_slot<T16>(s[k], e[k], L.lo, L.hi, a.B.nb + 1);
+                    int slot = slow_slot<T16>(slow_s<PK, EXP>(s[k]), e[k], L.lo, L.hi, a.B.nb + 1);
                     if constexpr (EXP) {
                         if (slot < 0)
                             slot = tight_slot<T16>(a, L, s[k], e[k], A, j + k);
@@ -546,7 +563,7 @@ __device__ __forceinline__ void chunk_f32(const SweepArgs &a, const Lds &L, lds_
             continue;
         int slot = e[k];
         if (__builtin_expect(is_slow<T16>(e[k]), 0)) {
-            slot = slow_slot<T16>(s[k], e[k], L.lo, L.hi, a.B.nb + 1);
+            slot = slow_slot<T16>(slow_s<PK, EXP>(s[k]), e[k], L.lo, L.hi, a.B.nb + 1);
             if constexpr (EXP) {
                 if (slot < 0)
                     slot = tight_slot<T16>(a, L, s[k], e[k], A, j + k);
@@ -884,8 +901,7 @@ __device__ __forceinline__ void chunk_f32_rppi_q(const SweepArgs &a, const Lds &
             s[k] = kmax;
             u[k] = 1u << (sh - 1);
         }
-        // s >= 0, so the bit patterns order like the values (no NaN here)
-        key[k] = tbl_key_f32<PK>(s[k], kmax);
+        key[k] = tbl_key_f32<PK, EXP>(s[k], kmax);
         near[k] = u[k] & mask;
         nmin = min(nmin, near[k]);
     }
@@ -905,7 +921,7 @@ __device__ __forceinline__ void chunk_f32_rppi_q(const SweepArgs &a, const Lds &
             if (sr || sp) {
                 int row = er[k];
                 if (sr) {
-                    row = slow_slot<T16>(s[k], er[k], L.lo, L.hi, nb + 1);
+                    row = slow_slot<T16>(slow_s<PK, EXP>(s[k]), er[k], L.lo, L.hi, nb + 1);
                     if constexpr (EXP) {
                         if (row < 0)
                             row = tight_slot<T16, 2>(a, L, s[k], er[k], A, j + k);
