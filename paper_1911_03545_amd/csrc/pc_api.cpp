@@ -564,7 +564,9 @@ cf_status radec_on_host(cf_ctx *c, const cf_catalog &cat, bool sky, double *vx, 
         if (k == 0)
             continue;
         pool.finish(k - 1);
-        if (bad.load() != UINT64_MAX)
+        // (a bad point of the slab now being converted waits for the points
+        // before it: the first one decides)
+        if (bad.load() < 2 * (uint64_t)k * slab)
             break;
         if ((st = store(k - 1)))
             return st;
@@ -572,9 +574,12 @@ cf_status radec_on_host(cf_ctx *c, const cf_catalog &cat, bool sky, double *vx, 
             return st;
     }
     const uint64_t b = bad.load();
-    if (b != UINT64_MAX)
+    if (b != UINT64_MAX) {
+        // (no copy out of the caller's columns is left queued)
+        HIPCHK(hipStreamSynchronize(c->stream));
         return b & 1 ? fail(c, CF_EINVAL, "distances must be finite and non-negative")
                      : fail(c, CF_ERANGE, "RA must lie in [0, 360] and DEC in [-90, 90]");
+    }
     return CF_OK;
 }
 
