@@ -108,8 +108,10 @@ typedef struct cf_options {
     int32_t slices_per_reach;   /* z slices per line-of-sight reach (0: 32;
                                    declination slices per band on the angular
                                    grid)                                       */
-    int32_t chunk;              /* max j points per work item (default 2048;
-                                   short work lists take shorter items)       */
+    int32_t chunk;              /* max j points per work item.  2048, the
+                                   default (also 0): short work lists of single
+                                   catalogues take shorter items; any other
+                                   value stands as given                       */
     int32_t output_on_device;   /* counts / wsum are device pointers           */
     int32_t theta_unit_vectors; /* theta input is unit vectors, not RA/DEC;
                                    on-sky (mocks) input is Cartesian positions,

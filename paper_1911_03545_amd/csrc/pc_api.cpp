@@ -778,6 +778,9 @@ int32_t item_margin(int32_t last)
     return cap <= (int64_t)0x7fffffff ? (int32_t)cap : 0;
 }
 
+// Longest work item by default, in j points (cf_options.chunk).
+constexpr int32_t kDefaultChunk = 2048;
+
 struct RunCtl {
     bool capture = false;
     bool no_async = false;  // eager call: read the work-item count before the sweep
@@ -1200,9 +1203,11 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // (88 -> 115 us), but no slower at 6.6*10^4, where the list takes 15 us in
     // place of 24.  (Batched calls meet their catalogues one after the other.)
     const bool ordered = priv || n1 + (autocorr ? 0 : n2) > 65536;
-    const int chunk_max = opt.chunk > 0 ? std::min(opt.chunk, 1 << 20) : 2048;
+    // (a length that the caller or the tuner asks for stands)
+    const bool auto_chunk = opt.chunk <= 0 || opt.chunk == kDefaultChunk;
+    const int chunk_max = auto_chunk ? kDefaultChunk : std::min(opt.chunk, 1 << 20);
     int chunk = chunk_max;
-    if (!priv && !sky_grid && !lean && opt.flush_pairs == 0) {
+    if (auto_chunk && !priv && !sky_grid && !lean && opt.flush_pairs == 0) {
         // (a caller that lowers the merge bound wants waves to reach it)
         // Shorter items where the whole list is short: about two items for
         // each resident wave (eight with weights, whose pairs take longer),
@@ -1221,7 +1226,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
                           (autocorr ? 0.5 : 1.0) * (2 * g.xyk + 1) * (2 * g.xyk + 1);
         const double each = js / ((weighted ? 8.0 : 2.0) * 32.0 * c->num_cu);
         if (each < chunk)
-            chunk = std::max(std::min(chunk, 64), ((int)each + 7) / 8 * 8);
+            chunk = std::max(64, ((int)each + 7) / 8 * 8);
     }
     if ((st2 = ensure(c, B_BLOCKS, sizeof(pc_block) * (size_t)nblocks)) ||
         (ordered && (st2 = ensure(c, B_ICNT, sizeof(int32_t) * (size_t)item_wgs))) ||
@@ -1910,7 +1915,7 @@ cf_status count(cf_ctx *c, int metric, bool theta, const cf_catalog *d1, int32_t
             // its default
             const bool tune_ang = theta && opt_in->angular_grid == 0;
             int32_t best_ang = tune_ang ? 16 : opt_in->angular_grid;
-            int32_t best_spr = 32, best_chunk = 2048;
+            int32_t best_spr = 32, best_chunk = kDefaultChunk;
             // x/y refinement of a 3-D grid, when left at its default
             const bool tune_xy = opt_in->xy_refine == 0 && !(theta && best_ang >= 0);
             int32_t best_xy = tune_xy ? 1 : opt_in->xy_refine;
@@ -2099,7 +2104,7 @@ void cf_default_options(cf_options *opt)
         return;
     memset(opt, 0, sizeof(*opt));
     opt->struct_size = (int32_t)sizeof(cf_options);
-    opt->chunk = 2048;
+    opt->chunk = kDefaultChunk;
 }
 
 cf_status cf_create(int device, void *hip_stream, cf_ctx **out)
