@@ -1916,17 +1916,18 @@ cf_status count(cf_ctx *c, int metric, bool theta, const cf_catalog *d1, int32_t
             const bool tune_ang = theta && opt_in->angular_grid == 0;
             int32_t best_ang = tune_ang ? 16 : opt_in->angular_grid;
             int32_t best_spr = 32, best_chunk = kDefaultChunk;
-            // x/y refinement of a 3-D grid, when left at its default
+            // x/y refinement of a 3-D grid, when left at its default: the
+            // planner's choice (0), then its neighbours
             const bool tune_xy = opt_in->xy_refine == 0 && !(theta && best_ang >= 0);
-            int32_t best_xy = tune_xy ? 1 : opt_in->xy_refine;
-            auto time_call = [&](int32_t spr, int32_t chunk, int32_t ang,
+            int32_t best_xy = opt_in->xy_refine;
+            auto time_call = [&](int32_t spr, int32_t chunk, int32_t ang, int32_t xy,
                                  double *ms) -> cf_status {
                 cf_options o = tuned_opt;
                 o.use_graph = 0;
                 o.slices_per_reach = spr;
                 o.chunk = chunk;
                 o.angular_grid = ang;
-                o.xy_refine = best_xy;
+                o.xy_refine = xy;
                 const auto t0 = std::chrono::steady_clock::now();
                 cf_status st = run(c, probe, metric, theta, d1, ncat, d2, edges, nb, pimax, npi,
                                    boxsize, prec, counts, wsum, &o);
@@ -1935,16 +1936,18 @@ cf_status count(cf_ctx *c, int metric, bool theta, const cf_catalog *d1, int32_t
                 return st;
             };
             double best = 0.0;
-            cf_status st = time_call(best_spr, best_chunk, best_ang, &best);   // warms buffers
+            // (the first call warms the buffers)
+            cf_status st = time_call(best_spr, best_chunk, best_ang, best_xy, &best);
             if (st != CF_OK)
                 return st;
-            if ((st = time_call(best_spr, best_chunk, best_ang, &best)))
+            const int32_t planned_xy = c->stats.xy_refine;
+            if ((st = time_call(best_spr, best_chunk, best_ang, best_xy, &best)))
                 return st;
             for (int32_t spr : {2, 4, 8, 16, 32}) {
                 if (spr == best_spr)
                     continue;
                 double ms;
-                if ((st = time_call(spr, best_chunk, best_ang, &ms)))
+                if ((st = time_call(spr, best_chunk, best_ang, best_xy, &ms)))
                     return st;
                 if (ms < best) {
                     best = ms;
@@ -1953,7 +1956,7 @@ cf_status count(cf_ctx *c, int metric, bool theta, const cf_catalog *d1, int32_t
             }
             for (int32_t chunk : {512, 1024, 4096, 8192}) {
                 double ms;
-                if ((st = time_call(best_spr, chunk, best_ang, &ms)))
+                if ((st = time_call(best_spr, chunk, best_ang, best_xy, &ms)))
                     return st;
                 if (ms < best) {
                     best = ms;
@@ -1963,23 +1966,25 @@ cf_status count(cf_ctx *c, int metric, bool theta, const cf_catalog *d1, int32_t
             if (tune_ang)
                 for (int32_t ang : {8, 32}) {
                     double ms;
-                    if ((st = time_call(best_spr, best_chunk, ang, &ms)))
+                    if ((st = time_call(best_spr, best_chunk, ang, best_xy, &ms)))
                         return st;
                     if (ms < best) {
                         best = ms;
                         best_ang = ang;
                     }
                 }
-            if (tune_xy) {
-                best_xy = 2;
-                double ms;
-                if ((st = time_call(best_spr, best_chunk, best_ang, &ms)))
-                    return st;
-                if (ms < best)
-                    best = ms;
-                else
-                    best_xy = 1;
-            }
+            if (tune_xy)
+                for (int32_t xy : {planned_xy - 1, planned_xy + 1}) {
+                    double ms;
+                    if (xy < 1 || xy > PC_MAX_XYK)
+                        continue;
+                    if ((st = time_call(best_spr, best_chunk, best_ang, xy, &ms)))
+                        return st;
+                    if (ms < best) {
+                        best = ms;
+                        best_xy = xy;
+                    }
+                }
             it = c->tuned.emplace(tk, cf_ctx::Tuned{best_spr, best_chunk, best_ang, best_xy})
                      .first;
         }
