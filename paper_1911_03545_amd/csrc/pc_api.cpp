@@ -771,10 +771,11 @@ void key_add(std::vector<char> &k, const void *p, size_t n)
 }
 
 // Work-item capacity for a call that does not read the count first: the
-// last count plus a quarter plus 1024, or 0 when that would not fit int32.
+// last count plus a quarter plus kItemRoom, or 0 when that would not fit int32.
+constexpr int32_t kItemRoom = 1024;
 int32_t item_margin(int32_t last)
 {
-    const int64_t cap = (int64_t)last + last / 4 + 1024;
+    const int64_t cap = (int64_t)last + last / 4 + kItemRoom;
     return cap <= (int64_t)0x7fffffff ? (int32_t)cap : 0;
 }
 
@@ -1558,9 +1559,12 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // stays on the device the last one, with a quarter of headroom, sizes the
     // launch (the waves take items until none are left, so it need not be
     // exact): every workgroup copies the table and merges a histogram, which
-    // a full grid paid for 1024 workgroups also when 230 had work
+    // a full grid paid for 1024 workgroups also when 230 had work.  No fewer
+    // than for the items that such a call always has room for: after a call of
+    // a handful of items, one of a thousand would run on one workgroup.
     const int64_t want_items = (ctl.capture || async_items)
-                                   ? (int64_t)c->last_items + c->last_items / 4
+                                   ? std::max((int64_t)c->last_items + c->last_items / 4,
+                                              (int64_t)kItemRoom)
                                    : (int64_t)n_items;
     int nwg = (int)std::min<int64_t>((want_items + waves - 1) / waves,
                                      (int64_t)c->num_cu * per_cu);
