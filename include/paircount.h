@@ -244,7 +244,9 @@ typedef struct cf_stats {
     int64_t n_blocks;           /* i-blocks of up to 64 points                 */
     int64_t n_items;            /* work items processed by the pair sweep      */
     uint64_t candidate_pairs;   /* pair evaluations performed by the sweep     */
-    uint64_t rechecks;          /* FP32 pairs re-evaluated in binary64         */
+    uint64_t rechecks;          /* FP32 pairs re-evaluated in binary64, and
+                                   pairs of cf_binary64_form 2 re-evaluated as
+                                   the definition writes them                  */
     int32_t sweep_workgroups;   /* persistent workgroups of the sweep launch   */
     int32_t hist_copies;        /* LDS histogram replicas per wave             */
     float t_prepare_ms;         /* validation, conversion, bounding box        */
@@ -289,6 +291,12 @@ cf_status cf_set_allocator(cf_ctx *ctx, cf_alloc_fn alloc, cf_free_fn free_, voi
    failing cf_create on this thread (never NULL). */
 const char *cf_last_error(const cf_ctx *ctx);
 cf_status cf_get_stats(const cf_ctx *ctx, cf_stats *out);
+/* *form: how the binary64 sweep of the last counting call on ctx formed its pairs: 1
+   as the definition writes them; 2 in fewer operations (unweighted DD(r) and chords:
+   |a|^2 + |b|^2 - 2 a.b; on-sky: from 2 s.v_i and a one-step reciprocal root), the
+   definition deciding every pair within the form's error bound of an edge; 0 when
+   no binary64 sweep ran (float32, empty or failed calls). */
+cf_status cf_binary64_form(const cf_ctx *ctx, int32_t *form);
 void cf_default_options(cf_options *opt);
 
 /* DD(r) -- Table 1 "xi(r)" / "DD": 3-D separations (Appendix A).
@@ -510,6 +518,20 @@ cf_status cf_fp32_bands_xy(const double *edges_sq, int32_t nedges, int32_t ndim,
    pointer, ndim other than 2 or 3, or a negative or non-finite value. */
 cf_status cf_fp32_pair_margin(const double *xy_max, int32_t ndim, double fscale, float *K,
                               float *M);
+
+/* Host-only: the bound of the expanded binary64 DD(r) sweep (cf_binary64_form 2)
+   for nedges edges and points with |a|^2 + |b|^2 <= mag: *bound on the difference
+   between its squared separation and the definition's, 0 where the form is not
+   taken (the bound is above 2^-12 of the smallest nonzero squared edge or 2^-18 of
+   the largest, or there are more than 125 bins), and *scale, its coordinate
+   scale (else 0). */
+cf_status cf_expand64_bound(const double *edges, int32_t nedges, double mag, double *bound,
+                            double *scale);
+/* Host-only: the bounds of the on-sky sweep's form 2 for points within sqrt(m2) of
+   the observer: *ds on the difference in rp^2, *dpi in pi; both 0 where the form is
+   not taken. */
+cf_status cf_mocks_bounds(const double *edges, int32_t nedges, double pimax, int32_t npi,
+                          double m2, double *ds, double *dpi);
 
 /* Host-only: the exact sum of n values p[k], each an integer multiple of 2^q
    with |p[k]| < 2^(q + 94), rounded once to binary64 (ties to even), through

@@ -43,7 +43,7 @@ EXPORTED_SYMBOLS = (
     "count_pairs_rppi_batch_ex", "count_pairs_rppi_mocks", "count_pairs_rppi_mocks_ex",
     "cf_plan_grid", "cf_plan_grid_ex", "cf_plan_sky_grid", "cf_fp32_bands",
     "cf_fp32_bands_axes", "cf_fp32_bands_xy", "cf_fp32_pair_margin",
-    "cf_fixed_sum",
+    "cf_fixed_sum", "cf_binary64_form", "cf_expand64_bound", "cf_mocks_bounds",
 )
 
 
@@ -193,6 +193,12 @@ def load_library(path: str = LIB_PATH):
     lib.cf_fp32_bands_xy.restype = ctypes.c_int
     lib.cf_fp32_pair_margin.argtypes = [vp, i32, dbl, vp, vp]
     lib.cf_fp32_pair_margin.restype = ctypes.c_int
+    lib.cf_binary64_form.argtypes = [vp, vp]
+    lib.cf_binary64_form.restype = ctypes.c_int
+    lib.cf_expand64_bound.argtypes = [vp, i32, dbl, vp, vp]
+    lib.cf_expand64_bound.restype = ctypes.c_int
+    lib.cf_mocks_bounds.argtypes = [vp, i32, dbl, i32, dbl, vp, vp]
+    lib.cf_mocks_bounds.restype = ctypes.c_int
     lib.cf_fixed_sum.argtypes = [vp, ctypes.c_int64, i32, vp]
     lib.cf_fixed_sum.restype = ctypes.c_int
     _lib = lib
@@ -331,6 +337,32 @@ def fp32_pair_margin(xy_max, fscale: float, ndim: int = 3):
     if st != CF_OK:
         raise PairCountError(st, "cf_fp32_pair_margin failed")
     return K[0], M[0]
+
+
+def expand64_bound(edges, mag: float):
+    """Host-only (bound, scale) of the expanded binary64 DD(r) sweep; the bound is
+    0 where the form is not taken."""
+    lib = load_library()
+    e = np.ascontiguousarray(edges, dtype=np.float64)
+    out = np.zeros(2)
+    st = lib.cf_expand64_bound(e.ctypes.data, e.size, float(mag), out.ctypes.data,
+                               out.ctypes.data + 8)
+    if st != CF_OK:
+        raise PairCountError(st, "cf_expand64_bound failed")
+    return out[0], out[1]
+
+
+def mocks_bounds(edges, pimax: float, npi: int, m2: float):
+    """Host-only (ds, dpi) of the on-sky sweep's form in fewer operations; 0 where
+    it is not taken."""
+    lib = load_library()
+    e = np.ascontiguousarray(edges, dtype=np.float64)
+    out = np.zeros(2)
+    st = lib.cf_mocks_bounds(e.ctypes.data, e.size, float(pimax), int(npi), float(m2),
+                             out.ctypes.data, out.ctypes.data + 8)
+    if st != CF_OK:
+        raise PairCountError(st, "cf_mocks_bounds failed")
+    return out[0], out[1]
 
 
 def fixed_sum(values, q: int) -> float:
@@ -681,6 +713,13 @@ class PairCounter:
             None if wsum is None else wsum.ctypes.data, optp)
         self._check(st)
         return self._result(counts, wsum, rv, (nb,))
+
+    def binary64_form(self) -> int:
+        """How the last call's binary64 sweep formed its pairs: 1 as the definition
+        writes them, 2 in fewer operations, 0 none ran."""
+        f = ctypes.c_int32(0)
+        self._check(self._lib.cf_binary64_form(self._ctx, ctypes.byref(f)))
+        return f.value
 
     def stats(self) -> dict:
         s = cf_stats()

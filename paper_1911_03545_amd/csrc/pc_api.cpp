@@ -89,6 +89,8 @@ struct cf_ctx {
     bool g_wsum = false;
     bool g_ravg = false;
     cf_stats gstats;
+    // form of the last call's binary64 sweep (cf_binary64_form), the graph's
+    int32_t form64 = 0, gform64 = 0;
     // autotuned choices per workload class
     struct Tuned {
         int32_t slices_per_reach, chunk, angular_grid, xy_refine;
@@ -800,8 +802,10 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     if (!c)
         return CF_EINVAL;
     c->err.clear();
-    if (!ctl.capture)
+    if (!ctl.capture) {
         memset(&c->stats, 0, sizeof(c->stats));
+        c->form64 = 0;
+    }
     cf_options opt;
     cf_default_options(&opt);
     if (opt_in) {
@@ -1685,6 +1689,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     S.angular_grid = opt.angular_grid;
     S.xy_refine = sky_grid ? 0 : g.xyk;
     S.separation_form = fp32 ? (xy_mag > 0.0 ? 2 : 1) : 0;
+    c->form64 = fp32 ? 0 : (exp_form ? 2 : 1);
     S.chunk = chunk_max;
     S.n_blocks = hcounts[1];
     S.n_items = hcounts[0];
@@ -1787,6 +1792,7 @@ cf_status replay(cf_ctx *c, uint64_t *counts, double *wsum, const cf_options &op
     }
     c->stats = c->gstats;
     c->stats.replayed = 1;
+    c->form64 = c->gform64;
     unsigned rqn = 0;
     unsigned long long cnd = 0;
     memcpy(&rqn, hm + M_RQCOUNT, 4);
@@ -1862,6 +1868,7 @@ void record_graph(cf_ctx *c, std::vector<char> &&key, const RunCtl &eager, int m
         c->g_wsum = wsum != nullptr && d1->w != nullptr;
         c->g_ravg = opt && opt->ravg != nullptr;
         c->gstats = keep;
+        c->gform64 = c->form64;
         return;
     }
     (void)hipGetLastError();
@@ -2238,6 +2245,14 @@ cf_status cf_get_stats(const cf_ctx *c, cf_stats *out)
     if (!c || !out)
         return CF_EINVAL;
     *out = c->stats;
+    return CF_OK;
+}
+
+cf_status cf_binary64_form(const cf_ctx *c, int32_t *form)
+{
+    if (!c || !form)
+        return CF_EINVAL;
+    *form = c->form64;
     return CF_OK;
 }
 

@@ -973,6 +973,26 @@ extern "C" cf_status cf_fp32_pair_margin(const double *xy_max, int32_t ndim, dou
     return CF_OK;
 }
 
+extern "C" cf_status cf_expand64_bound(const double *edges, int32_t nedges, double mag,
+                                       double *bound, double *scale)
+{
+    if (!edges || !bound || !scale || nedges < 2 || !(mag >= 0.0))
+        return CF_EINVAL;
+    *scale = 0.0;
+    *bound = pc::expand64(edges, nedges - 1, mag, scale);
+    return CF_OK;
+}
+
+extern "C" cf_status cf_mocks_bounds(const double *edges, int32_t nedges, double pimax,
+                                     int32_t npi, double m2, double *ds, double *dpi)
+{
+    if (!edges || !ds || !dpi || nedges < 2 || npi < 1 || !(pimax > 0.0) || !(m2 >= 0.0))
+        return CF_EINVAL;
+    if (!pc::mocks_bounds(edges, nedges - 1, pimax, npi, m2, ds, dpi))
+        *ds = *dpi = 0.0;
+    return CF_OK;
+}
+
 // Host twin of the fixed-point weight sums (pc_fixed.h): the same limb split,
 // limb sums and 192-bit assembly as the sweep and its merges, in one thread.
 extern "C" cf_status cf_fixed_sum(const double *p, int64_t n, int32_t q, double *out)

@@ -707,7 +707,8 @@ __device__ __forceinline__ void chunk_mocks(const SweepArgs &a, const Lds &L, ld
                                             lds_f64wp whb, double xi, double yi, double zi,
                                             double A4, LaneW wi, int i, const double *xs,
                                             const double *ys, const double *zs,
-                                            const double *ws, int j, int rem = CH)
+                                            const double *ws, int j, unsigned &rechecks,
+                                            int rem = CH)
 {
     double s[CH], pz[CH];
     int e[CH];
@@ -765,6 +766,7 @@ __device__ __forceinline__ void chunk_mocks(const SweepArgs &a, const Lds &L, ld
     while (und) {
         const int k = __ffs((int)und) - 1;
         und &= und - 1u;
+        rechecks++;
         const double xj = a.x2[j + k], yj = a.y2[j + k], zj = a.z2[j + k];
         const double dx = __dsub_rn(xi, xj), dy = __dsub_rn(yi, yj), dz = __dsub_rn(zi, zj);
         const double ss = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)),
@@ -799,7 +801,8 @@ template <bool TRI, bool UNC, int CH, bool MASK = false>
 __device__ __forceinline__ void chunk_r64(const SweepArgs &a, const Lds &L, lds_u32p hb,
                                           double ex, double ey, double ez, double A, int i,
                                           const double *xs, const double *ys, const double *zs,
-                                          const double *qs, int j, unsigned dcode, int rem = CH)
+                                          const double *qs, int j, unsigned dcode,
+                                          unsigned &rechecks, int rem = CH)
 {
     float s[CH];
     int e[CH];
@@ -829,8 +832,10 @@ __device__ __forceinline__ void chunk_r64(const SweepArgs &a, const Lds &L, lds_
         for (int k = 0; k < CH; k++) {
             if ((unsigned)e[k] >= PC_TBL8_BAND) {
                 int slot = slow_slot<false>(s[k], e[k], L.lo, L.hi, a.B.nb + 1);
-                if (slot < 0)
+                if (slot < 0) {
                     slot = exact_slot<PC_METRIC_R>(a, L, i, j + k, dcode);
+                    rechecks++;
+                }
                 e[k] = slot;
             }
         }
@@ -1189,7 +1194,7 @@ __device__ __forceinline__ void item_f32(const SweepArgs &a, const Lds &L, lds_u
 template <bool TRI, bool UNC>
 __device__ __forceinline__ void item_r64(const SweepArgs &a, const Lds &L, lds_u32p hb,
                                          int i, bool act, const LanePt &lp, int j0, int j1,
-                                         unsigned dcode)
+                                         unsigned dcode, unsigned &rechecks)
 {
     const double ax = lp.x + dval(dcode & 3u, a.L), ay = lp.y + dval((dcode >> 2) & 3u, a.L),
                  az = lp.z + dval((dcode >> 4) & 3u, a.L);
@@ -1209,7 +1214,7 @@ __device__ __forceinline__ void item_r64(const SweepArgs &a, const Lds &L, lds_u
             zs[k] = z2[j + k];
             qs[k] = q2[j + k];
         }
-        chunk_r64<TRI, UNC, CH>(a, L, hb, ex, ey, ez, A, i, xs, ys, zs, qs, j, dcode);
+        chunk_r64<TRI, UNC, CH>(a, L, hb, ex, ey, ez, A, i, xs, ys, zs, qs, j, dcode, rechecks);
     }
     if (j < j1) {
         const int rem = j1 - j;
@@ -1222,7 +1227,8 @@ __device__ __forceinline__ void item_r64(const SweepArgs &a, const Lds &L, lds_u
             zs[k] = z2[jk];
             qs[k] = q2[jk];
         }
-        chunk_r64<TRI, UNC, CH, true>(a, L, hb, ex, ey, ez, A, i, xs, ys, zs, qs, j, dcode, rem);
+        chunk_r64<TRI, UNC, CH, true>(a, L, hb, ex, ey, ez, A, i, xs, ys, zs, qs, j, dcode,
+                                      rechecks, rem);
     }
 }
 
@@ -1230,7 +1236,7 @@ __device__ __forceinline__ void item_r64(const SweepArgs &a, const Lds &L, lds_u
 template <int M, int W, bool TRI, bool OFS, bool T16, bool UNC, bool FAST>
 __device__ __forceinline__ void item_f64(const SweepArgs &a, const Lds &L, lds_u32p hb,
                                          lds_f64wp whb, int i, bool act, int j0, int j1,
-                                         unsigned dcode)
+                                         unsigned dcode, unsigned &rechecks)
 {
     const double Dx = dval(dcode & 3u, a.L), Dy = dval((dcode >> 2) & 3u, a.L),
                  Dz = dval((dcode >> 4) & 3u, a.L);
@@ -1253,7 +1259,8 @@ __device__ __forceinline__ void item_f64(const SweepArgs &a, const Lds &L, lds_u
             ws[k] = W ? w2[j + k] : 0.0;
         }
         if constexpr (FAST)
-            chunk_mocks<W, TRI, T16, CH>(a, L, hb, whb, xi, yi, zi, A4, wi, i, xs, ys, zs, ws, j);
+            chunk_mocks<W, TRI, T16, CH>(a, L, hb, whb, xi, yi, zi, A4, wi, i, xs, ys, zs, ws, j,
+                                         rechecks);
         else
             chunk_f64<M, W, TRI, OFS, T16, UNC, CH>(a, L, hb, whb, xi, yi, zi, Dx, Dy, Dz, wi, i,
                                                     xs, ys, zs, ws, j);
@@ -1272,7 +1279,7 @@ __device__ __forceinline__ void item_f64(const SweepArgs &a, const Lds &L, lds_u
         }
         if constexpr (FAST)
             chunk_mocks<W, TRI, T16, CH, true>(a, L, hb, whb, xi, yi, zi, A4, wi, i, xs, ys, zs,
-                                               ws, j, rem);
+                                               ws, j, rechecks, rem);
         else
             chunk_f64<M, W, TRI, OFS, T16, UNC, CH, true>(a, L, hb, whb, xi, yi, zi, Dx, Dy, Dz,
                                                           wi, i, xs, ys, zs, ws, j, rem);
@@ -1530,7 +1537,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     const unsigned long long flush_at = a.flush_at;
     unsigned cur_cat = 0;
 
-    unsigned rechecks = 0;   // pairs this lane settled in binary64
+    unsigned rechecks = 0;   // pairs this lane settled by the binary64 definition
     // wave-uniform (kept in a scalar register, so every item field and j
     // index derived from it stays scalar)
     int stream = __builtin_amdgcn_readfirstlane(
@@ -1660,9 +1667,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 }
                 const int tm = tri ? tri_end<0>(it.j0, it.j1, it.i0 + ni) : it.j0;
                 if (tm > it.j0)
-                    item_r64<true, UNC>(a, L, hb, i, act, lp, it.j0, tm, dcode);
+                    item_r64<true, UNC>(a, L, hb, i, act, lp, it.j0, tm, dcode, rechecks);
                 if (it.j1 > tm)
-                    item_r64<false, UNC>(a, L, hb, i, act, lp, tm, it.j1, dcode);
+                    item_r64<false, UNC>(a, L, hb, i, act, lp, tm, it.j1, dcode, rechecks);
                 continue;
             }
             if (PIPE && (it.i0 != lp_i0 || ni != lp_ni)) {
@@ -1684,14 +1691,15 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             const int tm = tri ? tri_end<W>(it.j0, it.j1, it.i0 + ni) : it.j0;
             constexpr bool FAST = M == PC_METRIC_MOCKS && EXP;
             if (tm > it.j0)
-                item_f64<M, W, true, false, T16, UNC, FAST>(a, L, hb, whb, i, act, it.j0, tm, dcode);
+                item_f64<M, W, true, false, T16, UNC, FAST>(a, L, hb, whb, i, act, it.j0, tm, dcode,
+                                                            rechecks);
             if (it.j1 > tm) {
                 if (dcode == 0u)
                     item_f64<M, W, false, false, T16, UNC, FAST>(a, L, hb, whb, i, act, tm, it.j1,
-                                                           dcode);
+                                                                 dcode, rechecks);
                 else
                     item_f64<M, W, false, true, T16, UNC, FAST>(a, L, hb, whb, i, act, tm, it.j1,
-                                                          dcode);
+                                                                dcode, rechecks);
             }
         }
     }
@@ -1705,7 +1713,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         __syncthreads();
         flush_hist<UNC>(a, L, (int)threadIdx.x, kSweepThreads, W, 0u);
     }
-    if (P32 && !D64) {
+    if (P32 || EXP) {
         // one atomic per wave for the recheck statistic
         unsigned tot = rechecks;
         for (int off = PC_WAVE / 2; off > 0; off >>= 1)
