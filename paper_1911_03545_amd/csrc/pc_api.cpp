@@ -1179,11 +1179,11 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // On-sky pairs: formed in fewer operations where the observer's distance
     // and the bins allow it (the mean separation takes the root of rp^2 and
     // keeps the definition's order)
-    double mk_ds = 0.0, mk_dpi = 0.0, mk_m2 = 0.0;
+    double mk_ds = 0.0, mk_dpi = 0.0, mk_m2 = 0.0, mk_ll = 0.0;
     if (sky && !want_ravg) {
         for (int a = 0; a < 3; a++)
             mk_m2 += std::max(lo[a] * lo[a], hi[a] * hi[a]);
-        if (!pc::mocks_bounds(lin.data(), nb, pimax, npi, mk_m2, &mk_ds, &mk_dpi))
+        if (!pc::mocks_bounds(lin.data(), nb, pimax, npi, mk_m2, &mk_ds, &mk_dpi, &mk_ll))
             mk_ds = 0.0;
     }
     g.fscale = fscale;
@@ -1453,7 +1453,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         exp_form = tau < 0.25;
         a.mk_tau = (float)(tau * (1.0 + 0x1p-20));
         a.mk_lim = (hb.hdr.E_top + pimax * pimax) * (1.0 + 0x1p-30);
-        a.mk_ll = mk_m2 / 16.0;
+        a.mk_ll = mk_ll;
         a.mk_E = hb.hdr.E_top + mk_ds;
         a.mk_pi = pimax + mk_dpi;
     }

@@ -67,7 +67,7 @@ struct SweepArgs {
     int32_t xy_exp;
     // on-sky sweep: a pair whose s.s is at most mk_lim is formed in fewer
     // operations, off by at most mk_ds in rp^2 and mk_dpi in pi while |L|^2 is at
-    // least mk_ll; mk_tau is the margin of its fast pi bin
+    // least |v_i|^2 / 4 + mk_ll; mk_tau is the margin of its fast pi bin
     double mk_lim, mk_ll, mk_E, mk_pi;
     float mk_tau;
     const double *q2;

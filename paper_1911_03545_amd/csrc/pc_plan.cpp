@@ -601,14 +601,20 @@ int fp32_scale(int metric, const double *edges, int nb, double coord_scale, bool
 // 2 s.v_i - sl (s = v_i - v_j, L = v_i + v_j = 2 v_i - s), the reciprocal root
 // of ll by one Newton step from v_rsq_f64 (documented to 2^29 ulp, so 2^-45
 // after the step), pi = |sl| / |L| and rp^2 = s.s - pi^2.  With R^2 the largest
-// s.s that can be in range, M the largest distance from the observer and ll >=
-// M^2 / 16, in units of u = 2^-53: sl is off by at most 32 R M (both forms'
-// roundings), so pi by 128 R; ll by 40 M^2, 640 relative, so pi by 320 R; the
-// root's 2^-45 is 256 R.  2^-38 R = 2^15 u R is far above their sum, and 2^-36
-// R^2 above the error of rp^2 (2 R times that, and 8 u R^2).  Pairs within
-// these of an edge, or with a smaller ll, are decided by the definition.
+// s.s that can be in range, V = |v_i| and ll >= V^2 / 4 (so V <= 2 |L| and |s| <=
+// 2 V + |L| <= 5 |L|), in units of u = 2^-53: 2 s.v_i is off by at most 8 |s| V,
+// s.s by 5 |s|^2 and the definition's s.L by 6 |s| |L|, so sl by 48 |s| |L| and
+// pi by 48 R; 4 V^2 by 12 V^2, the two differences by 37 |L|^2, so ll by 375
+// |L|^2, and pi by 188 R; the root's 2^-45 is 256 R, the definition's ll, root
+// and division 6 R.  2^-38 R = 2^15 u R is far above their sum, and 2^-36 R^2
+// above the error of rp^2 (2 R times that, and 15 u R^2).  Pairs within these of
+// an edge, or with a smaller ll, are decided by the definition.  The bound on ll
+// goes by the lane's own point: by the farthest point of the call (ll >= M^2 /
+// 16), catalogues with most points nearer than M / 8 took the definition for
+// nearly all pairs (3*10^5 points at 500 to 1500 with one at 3*10^4: sweep 2.64
+// ms, the definition alone 1.63).  ll_min keeps ll far from underflow.
 bool mocks_bounds(const double *edges, int nb, double pimax, int npi, double m2, double *ds,
-                  double *dpi)
+                  double *dpi, double *ll_min)
 {
     const double R2 = (edges[nb] * edges[nb] + pimax * pimax) * (1.0 + 0x1p-29);
     double emin = edges[nb] * edges[nb];
@@ -617,6 +623,7 @@ bool mocks_bounds(const double *edges, int nb, double pimax, int npi, double m2,
             emin = std::min(emin, edges[k] * edges[k]);
     *ds = 0x1p-36 * R2;
     *dpi = 0x1p-38 * std::sqrt(R2);
+    *ll_min = 0x1p-60 * R2;
     // worth it while few pairs are undecided; and with room for every square
     return *ds <= 0x1p-10 * emin && *dpi * npi <= 0x1p-10 * pimax && m2 >= R2 * 0x1p-20 &&
            m2 < 0x1p200 && m2 > 0x1p-200 && R2 > 0x1p-200;
@@ -988,7 +995,8 @@ extern "C" cf_status cf_mocks_bounds(const double *edges, int32_t nedges, double
 {
     if (!edges || !ds || !dpi || nedges < 2 || npi < 1 || !(pimax > 0.0) || !(m2 >= 0.0))
         return CF_EINVAL;
-    if (!pc::mocks_bounds(edges, nedges - 1, pimax, npi, m2, ds, dpi))
+    double ll_min;
+    if (!pc::mocks_bounds(edges, nedges - 1, pimax, npi, m2, ds, dpi, &ll_min))
         *ds = *dpi = 0.0;
     return CF_OK;
 }

@@ -63,10 +63,11 @@ int fp32_scale(int metric, const double *edges, int nb, double coord_scale, bool
 int build_bins(int metric, bool fp32, const double *edges, int nb, double pimax, int npi,
                double coord_scale, const double *axis_eps, double fscale, bool priv,
                double xy_mag, HostBins *out, double d64 = 0.0);
-// On-sky pairs formed from 2 s.v_i: bounds of the error in rp^2 and pi for
-// points within sqrt(m2) of the observer (false: the form is not taken)
+// On-sky pairs formed from 2 s.v_i: bounds of the error in rp^2 and pi of pairs
+// with |L|^2 >= |v_i|^2 / 4 + ll_min, for points within sqrt(m2) of the observer
+// (false: the form is not taken)
 bool mocks_bounds(const double *edges, int nb, double pimax, int npi, double m2, double *ds,
-                  double *dpi);
+                  double *dpi, double *ll_min);
 // Bound d64 of the expanded binary64 r sweep for coordinates of squared
 // magnitudes |a|^2 + |b|^2 <= mag, and its coordinate scale; 0 where the form
 // does not pay (see the definition)

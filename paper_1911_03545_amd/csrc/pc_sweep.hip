@@ -705,10 +705,10 @@ __device__ __forceinline__ void chunk_f64(const SweepArgs &a, const Lds &L, lds_
 template <int W, bool TRI, bool T16, int CH, bool MASK = false>
 __device__ __forceinline__ void chunk_mocks(const SweepArgs &a, const Lds &L, lds_u32p hb,
                                             lds_f64wp whb, double xi, double yi, double zi,
-                                            double A4, LaneW wi, int i, const double *xs,
-                                            const double *ys, const double *zs,
-                                            const double *ws, int j, unsigned &rechecks,
-                                            int rem = CH)
+                                            double A4, double ll_min, LaneW wi, int i,
+                                            const double *xs, const double *ys,
+                                            const double *zs, const double *ws, int j,
+                                            unsigned &rechecks, int rem = CH)
 {
     double s[CH], pz[CH];
     int e[CH];
@@ -733,7 +733,7 @@ __device__ __forceinline__ void chunk_mocks(const SweepArgs &a, const Lds &L, ld
             const double p = fabs(sl) * r;
             const double q = fma(-p, p, ss);
             // (not greater or equal: also a negative ll, whose root is NaN)
-            const bool bad = !(ll >= a.mk_ll);
+            const bool bad = !(ll >= ll_min);
             if (c && bad)
                 und |= 1u << k;
             if (c && !bad && q < a.mk_E && p < a.mk_pi) {
@@ -1248,6 +1248,7 @@ __device__ __forceinline__ void item_f64(const SweepArgs &a, const Lds &L, lds_u
     constexpr int CH = W ? 4 : 8;
     // (an inactive lane's separations overflow: out of range, never undecided)
     const double A4 = FAST ? 4.0 * ((xi * xi + yi * yi) + zi * zi) : 0.0;
+    const double ll_min = FAST ? fma(A4, 0.0625, a.mk_ll) : 0.0;
     int j = j0;
     for (; j + CH <= j1; j += CH) {
         double xs[CH], ys[CH], zs[CH], ws[CH];
@@ -1259,8 +1260,8 @@ __device__ __forceinline__ void item_f64(const SweepArgs &a, const Lds &L, lds_u
             ws[k] = W ? w2[j + k] : 0.0;
         }
         if constexpr (FAST)
-            chunk_mocks<W, TRI, T16, CH>(a, L, hb, whb, xi, yi, zi, A4, wi, i, xs, ys, zs, ws, j,
-                                         rechecks);
+            chunk_mocks<W, TRI, T16, CH>(a, L, hb, whb, xi, yi, zi, A4, ll_min, wi, i, xs, ys, zs,
+                                         ws, j, rechecks);
         else
             chunk_f64<M, W, TRI, OFS, T16, UNC, CH>(a, L, hb, whb, xi, yi, zi, Dx, Dy, Dz, wi, i,
                                                     xs, ys, zs, ws, j);
@@ -1278,8 +1279,8 @@ __device__ __forceinline__ void item_f64(const SweepArgs &a, const Lds &L, lds_u
             ws[k] = W ? w2[jk] : 0.0;
         }
         if constexpr (FAST)
-            chunk_mocks<W, TRI, T16, CH, true>(a, L, hb, whb, xi, yi, zi, A4, wi, i, xs, ys, zs,
-                                               ws, j, rechecks, rem);
+            chunk_mocks<W, TRI, T16, CH, true>(a, L, hb, whb, xi, yi, zi, A4, ll_min, wi, i, xs,
+                                               ys, zs, ws, j, rechecks, rem);
         else
             chunk_f64<M, W, TRI, OFS, T16, UNC, CH, true>(a, L, hb, whb, xi, yi, zi, Dx, Dy, Dz,
                                                           wi, i, xs, ys, zs, ws, j, rem);

@@ -140,3 +140,33 @@ def test_on_sky_limits():
     assert pc.mocks_bounds(e, 40.0, 40, 1e-4) == (0.0, 0.0)
     assert pc.mocks_bounds(e, 40.0, 40, 2.0 ** 201) == (0.0, 0.0)
     assert pc.mocks_bounds(e * 1e-70, 4e-69, 40, 1e-134) == (0.0, 0.0)
+
+
+@pytest.mark.parametrize("V,spread", [(0.0, 1.0), (1e-3, 1.0), (1.0, 10.0), (30.0, 47.0),
+                                      (47.0, 47.0), (1e3, 47.0), (1e5, 47.0)])
+def test_on_sky_bounds_by_the_lane(V, spread):
+    """The bounds hold for every pair with |L|^2 >= |v_i|^2 / 4 + 2^-60 R^2, however far
+    the farthest point of the call lies: lanes at the observer, near it against the
+    reach and far from it, pairs on one side of the observer and across it."""
+    edges, pimax, npi = np.logspace(-1.0, np.log10(25.0), 10), 40.0, 40
+    R2 = edges[-1] ** 2 + pimax ** 2
+    ds, dpi = pc.mocks_bounds(edges, pimax, npi, 1e12)
+    rng = synth.rng_for(int(V + spread))
+    v = rng.normal(size=(3000, 3))
+    v *= V / np.linalg.norm(v, axis=1)[:, None]
+    w = rng.normal(size=v.shape)
+    w *= (spread * 10.0 ** rng.uniform(-3, 0, len(w)) / np.linalg.norm(w, axis=1))[:, None]
+    w[::4] = -2.0 * v[::4] * (1.0 - rng.uniform(-0.6, 0.6, len(w[::4])))[:, None]   # across
+    worst, used = [0.0, 0.0], 0
+    for k in range(len(v)):
+        vi, vj = v[k].tolist(), (v[k] + w[k]).tolist()
+        if not (w[k] ** 2).sum() < R2 or not np.any(v[k] * 2 + w[k]):
+            continue
+        form, exact, ll = on_sky(vi, vj, (1, -1)[k & 1] * 2.0 ** -23)
+        if not ll >= float((v[k] ** 2).sum()) / 4 + 2.0 ** -60 * R2:
+            continue
+        used += 1
+        worst[0] = max(worst[0], abs(form[0] - exact[0]) / dpi)
+        worst[1] = max(worst[1], abs(form[1] - exact[1]) / ds)
+    print("on-sky lanes at", V, ": shares of the bounds (pi, rp^2)", worst, used)
+    assert used > 500 and worst[0] < 0.125 and worst[1] < 0.125
