@@ -22,6 +22,7 @@
 #include "pc_common.h"
 #include "pc_launch.h"
 #include "pc_plan.h"
+#include "pc_slabs.h"
 
 namespace {
 
@@ -68,9 +69,8 @@ struct cf_ctx {
     DevBuf buf[B_COUNT];
     void *pinned = nullptr;
     size_t pinned_cap = 0;
-    // pinned slabs of the RA/DEC conversion on the host, with an event each
-    void *slabs = nullptr;
-    size_t slab_cap = 0;
+    // slabs of the RA/DEC conversion on the host, with an event each
+    pc::HostSlabs slabs;
     hipEvent_t slab_ev[3] = {};
     hipEvent_t ev[8] = {};
     int num_cu = 256;
@@ -440,7 +440,17 @@ private:
     std::vector<std::thread> pool_;
 };
 
-// Pinned slabs of the conversion: kSlabs of kSlabPoints points, each with its
+hipError_t pin_host(void **p, size_t bytes)
+{
+    const hipError_t e = hipHostMalloc(p, bytes, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
+// Slabs of the conversion: kSlabs of kSlabPoints points, each with its
 // input columns and its vectors (at most 19 MB; kept by the context).
 constexpr size_t kSlabs = 3, kSlabPoints = 131072;
 
@@ -466,24 +476,15 @@ cf_status radec_on_host(cf_ctx *c, const cf_catalog &cat, bool sky, double *vx, 
     const size_t nslab = (n + slab - 1) / slab;
     const size_t bytes = 6 * sizeof(double) * slab;
     const size_t want = std::min(kSlabs, nslab) * bytes;
-    if (c->slab_cap < want) {
-        if (c->slabs) {
-            HIPCHK(hipStreamSynchronize(c->stream));
-            HIPCHK(hipHostFree(c->slabs));
-            c->slabs = nullptr;
-            c->slab_cap = 0;
-        }
-        if (hipHostMalloc(&c->slabs, want, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            c->slabs = nullptr;
-            return fail(c, CF_ENOMEM, "hipHostMalloc(%zu) failed", want);
-        }
-        c->slab_cap = want;
+    if (c->slabs.size() < want) {
+        HIPCHK(hipStreamSynchronize(c->stream));
+        if (!c->slabs.grow(want, pin_host, hipHostFree))
+            return fail(c, CF_ENOMEM, "no host memory for %zu bytes of slabs", want);
     }
     for (auto &e : c->slab_ev)
         if (!e)
             HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    char *base = static_cast<char *>(c->slabs);
+    char *base = c->slabs.data();
     // inputs and vectors of the slab that holds point i
     auto in_of = [&](size_t k) { return base + (k % kSlabs) * bytes; };
     auto out_of = [&](size_t k) {
@@ -539,6 +540,8 @@ cf_status radec_on_host(cf_ctx *c, const cf_catalog &cat, bool sky, double *vx, 
                                   static_cast<const char *>(src[col]) + item * s0, item * m,
                                   hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipEventRecord(c->slab_ev[k % kSlabs], c->stream));
+        if (!c->slabs.pinned())
+            HIPCHK(hipStreamSynchronize(c->stream));
         return CF_OK;
     };
     auto store = [&](size_t k) -> cf_status {
@@ -547,6 +550,8 @@ cf_status radec_on_host(cf_ctx *c, const cf_catalog &cat, bool sky, double *vx, 
         for (int a = 0; a < 3; a++)
             HIPCHK(hipMemcpyAsync(dst[a] + s0, out_of(k) + (size_t)a * slab, sizeof(double) * m,
                                   hipMemcpyHostToDevice, c->stream));
+        if (!c->slabs.pinned())
+            HIPCHK(hipStreamSynchronize(c->stream));
         return CF_OK;
     };
     cf_status st;
@@ -2199,8 +2204,7 @@ cf_status cf_destroy(cf_ctx *c)
         (void)hipHostFree(c->gpin);
     if (c->cap_stream)
         (void)hipStreamDestroy(c->cap_stream);
-    if (c->slabs)
-        (void)hipHostFree(c->slabs);
+    c->slabs.release(hipHostFree);
     for (auto &ev : c->slab_ev)
         if (ev)
             (void)hipEventDestroy(ev);
