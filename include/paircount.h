@@ -441,6 +441,15 @@ cf_status cf_plan_grid_ex(const double lo[3], const double hi[3], double boxsize
                           int32_t xy_refine, int32_t ball, cf_grid_plan *out, int16_t *zro,
                           int32_t *k_used);
 
+/* The x/y refinement *k (1..4) that a 3-D call of n1 and n2 points (autocorr: the
+   same catalogue) takes by default on the grids above: the one with the least
+   expected sweep work, points spread evenly, each work item costing item_cost
+   pairs besides its own. */
+cf_status cf_plan_refine(const double lo[3], const double hi[3], double boxsize,
+                         double reach_xy, double reach_z, int32_t slices_per_reach,
+                         int32_t ball, double n1, double n2, int32_t autocorr,
+                         double item_cost, int32_t *k);
+
 /* Angular grid plan (host only, no device work) -- see
    cf_options.angular_grid.  chord_reach: the largest chord 2 sin(theta_max/2)
    of the bins; zlo, zhi: range of the unit vectors' z components (the

@@ -41,7 +41,7 @@ EXPORTED_SYMBOLS = (
     "count_pairs_rppi_ex",
     "count_pairs_theta", "count_pairs_theta_ex", "count_pairs_rppi_batch",
     "count_pairs_rppi_batch_ex", "count_pairs_rppi_mocks", "count_pairs_rppi_mocks_ex",
-    "cf_plan_grid", "cf_plan_grid_ex", "cf_plan_sky_grid", "cf_fp32_bands",
+    "cf_plan_grid", "cf_plan_grid_ex", "cf_plan_refine", "cf_plan_sky_grid", "cf_fp32_bands",
     "cf_fp32_bands_axes", "cf_fp32_bands_xy", "cf_fp32_pair_margin",
     "cf_fixed_sum", "cf_binary64_form", "cf_expand64_bound", "cf_mocks_bounds",
 )
@@ -193,6 +193,8 @@ def load_library(path: str = LIB_PATH):
     lib.cf_fp32_bands_xy.restype = ctypes.c_int
     lib.cf_fp32_pair_margin.argtypes = [vp, i32, dbl, vp, vp]
     lib.cf_fp32_pair_margin.restype = ctypes.c_int
+    lib.cf_plan_refine.argtypes = [vp, vp, dbl, dbl, dbl, i32, i32, dbl, dbl, i32, dbl, vp]
+    lib.cf_plan_refine.restype = ctypes.c_int
     lib.cf_binary64_form.argtypes = [vp, vp]
     lib.cf_binary64_form.restype = ctypes.c_int
     lib.cf_expand64_bound.argtypes = [vp, i32, dbl, vp, vp]
@@ -337,6 +339,25 @@ def fp32_pair_margin(xy_max, fscale: float, ndim: int = 3):
     if st != CF_OK:
         raise PairCountError(st, "cf_fp32_pair_margin failed")
     return K[0], M[0]
+
+
+def plan_refine(lo, hi, boxsize: float, reach_xy: float, reach_z: float, n1: float,
+                n2: float | None = None, item_cost: float = 2500.0, slices_per_reach: int = 32,
+                ball: bool = True) -> int:
+    """Host-only x/y refinement that a 3-D call takes by default (n2 None: an
+    autocorrelation)."""
+    lib = load_library()
+    lo, hi = (None if v is None else np.ascontiguousarray(v, dtype=np.float64)
+              for v in (lo, hi))
+    k = ctypes.c_int32(0)
+    st = lib.cf_plan_refine(None if lo is None else lo.ctypes.data,
+                            None if hi is None else hi.ctypes.data, float(boxsize),
+                            float(reach_xy), float(reach_z), int(slices_per_reach), int(ball),
+                            float(n1), float(n1 if n2 is None else n2), int(n2 is None),
+                            float(item_cost), ctypes.byref(k))
+    if st != CF_OK:
+        raise PairCountError(st, "cf_plan_refine failed")
+    return k.value
 
 
 def expand64_bound(edges, mag: float):

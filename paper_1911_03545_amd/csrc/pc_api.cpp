@@ -1061,8 +1061,8 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
         opt.xy_refine = (theta || ncat > 1 || lean)
                             ? 1
                             : pc::choose_refine(lo, hi, boxsize, reach_xy, reach_z,
-                                                metric != PC_METRIC_RPPI, (double)n1, (double)n2,
-                                                autocorr,
+                                                metric != PC_METRIC_RPPI, opt.slices_per_reach,
+                                                (double)n1, (double)n2, autocorr,
                                                 (sky || metric == PC_METRIC_RPPI ? 2000.0
                                                  : weighted                      ? 4300.0
                                                                                  : 2500.0) *

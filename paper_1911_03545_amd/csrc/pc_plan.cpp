@@ -80,65 +80,6 @@ int plan_grid_k(const double lo_in[3], const double hi_in[3], double boxsize,
 // smallest transverse distance between the two columns ((|o| - 1) column
 // widths per axis, less a margin of 2^-30 of the extent); columns no pair can
 // reach are skipped.
-// A block of 64 points of a column w wide spans b = 64 / (rho w^2) in z and
-// meets, in each neighbour column whose transverse gap is d, the points of 2
-// z(d) + b, z(d) = sqrt(reach^2 - d^2) for a ball; each column costs a work
-// item besides.  Narrower columns follow the reach more closely, but a block
-// grows longer and its items more and shorter.  Measured at k = 1 and 2 (sweep
-// of 10^6 points at density 0.0135, reach 25): DD(r) 623 and 626 us, DD(rp, pi)
-// 1377 and 1248; 4*10^6 weighted points (density 0.003, reach 50) 6.80 and 6.06
-// ms; solved for the cost of an item: 2000 (rp, pi) to 4300 (weighted) pairs,
-// half of that where pairs are formed in binary64 (DD(r) 958 and 833 us, on-sky
-// 8.7 and 6.0 ms).
-// Each further k adds about 16 us of gridding and listing at 10^6 points (6000
-// pairs a block).  Short lists (below 2*10^8 pairs) wait for latency, not work.
-int choose_refine(const double lo[3], const double hi[3], double boxsize, double reach_xy,
-                  double reach_z, bool zball, double n1, double n2, bool autocorr,
-                  double item_cost)
-{
-    double ext[3], vol = 1.0;
-    for (int a = 0; a < 3; a++) {
-        ext[a] = boxsize > 0.0 ? boxsize : hi[a] - lo[a];
-        vol *= ext[a];
-    }
-    if (!(vol > 0.0) || !(reach_xy > 0.0) || !std::isfinite(vol))
-        return 1;
-    const double rho1 = n1 / vol, rho2 = n2 / vol;
-    int best = 1;
-    double least = 0.0;
-    for (int k = 1; k <= PC_MAX_XYK; k++) {
-        double w[2];
-        for (int a = 0; a < 2; a++) {
-            const double n = std::floor(ext[a] / (reach_xy / k));
-            if (n < 2 * k + 1)
-                return best;   // (too few columns to refine)
-            w[a] = ext[a] / n;
-        }
-        const double area = w[0] * w[1];
-        const double b = std::min(PC_BLOCK_I / (rho1 * area), ext[2]);
-        double cost = 6000.0 * (k - 1);
-        for (int ox = -k; ox <= k; ox++)
-            for (int oy = -k; oy <= k; oy++) {
-                const double dx = std::max(std::abs(ox) - 1, 0) * w[0];
-                const double dy = std::max(std::abs(oy) - 1, 0) * w[1];
-                const double d2 = dx * dx + dy * dy;
-                if (d2 >= reach_xy * reach_xy)
-                    continue;
-                const double z = zball ? std::sqrt(reach_xy * reach_xy - d2) : reach_z;
-                const double run = rho2 * area * std::min(2.0 * z + b, ext[2]);
-                cost += PC_BLOCK_I * run + item_cost;
-            }
-        if (k == 1 && cost * n1 / PC_BLOCK_I * (autocorr ? 0.5 : 1.0) < 2e8)
-            return 1;
-        // (a few percent: the estimate's own worth)
-        if (k == 1 || cost < 0.97 * least) {
-            least = cost;
-            best = k;
-        }
-    }
-    return best;
-}
-
 int plan_grid(const double lo_in[3], const double hi_in[3], double boxsize,
               double reach_xy, double reach_z, int slices_per_reach,
               pc_grid *g, int xy_refine, bool zball)
@@ -231,6 +172,76 @@ int plan_grid_k(const double lo_in[3], const double hi_in[3], double boxsize,
             g->zro[a][b] = (int16_t)zr;
         }
     return CF_OK;
+}
+
+// A block of 64 points of a column w wide spans b = 64 / (rho w^2) in z and
+// meets, in each neighbour column whose transverse gap is d, the points of 2
+// z(d) + b, z(d) = sqrt(reach^2 - d^2) for a ball; each column costs a work
+// item besides.  Narrower columns follow the reach more closely, but a block
+// grows longer and its items more and shorter.  Measured at k = 1 and 2 (sweep
+// of 10^6 points at density 0.0135, reach 25): DD(r) 623 and 626 us, DD(rp, pi)
+// 1377 and 1248; 4*10^6 weighted points (density 0.003, reach 50) 6.80 and 6.06
+// ms; solved for the cost of an item: 2000 (rp, pi) to 4300 (weighted) pairs,
+// half of that where pairs are formed in binary64 (DD(r) 958 and 833 us, on-sky
+// 8.7 and 6.0 ms).
+// Each further k adds about 16 us of gridding and listing at 10^6 points (6000
+// pairs a block).  Short lists (below 2*10^8 pairs) wait for latency, not work.
+// Over 74 workloads (5*10^4 to 4*10^7 points, reach a fifth to a fiftieth of the
+// box, DD(r), (rp, pi), on-sky, weighted, mean separations, cross, both
+// precisions) the choice was at most 3.5% slower than k = 1 (2*10^5 points at
+// density 0.0128, reach 25: 256 and 248 us), 4 to 30% faster wherever it was not
+// 1, and within 5% of the best k but for weighted binary64 DD(r) (1.56 ms, 1.37
+// at 2) and on-sky pairs (2.96, 2.67 at 3).
+// The grids priced are those that plan_grid builds: columns no narrower than
+// its 1024 an axis allow, and slices as far apart as its cells allow.
+int choose_refine(const double lo[3], const double hi[3], double boxsize, double reach_xy,
+                  double reach_z, bool zball, int slices_per_reach, double n1, double n2,
+                  bool autocorr, double item_cost)
+{
+    double ext[3], vol = 1.0;
+    for (int a = 0; a < 3; a++) {
+        ext[a] = boxsize > 0.0 ? boxsize : hi[a] - lo[a];
+        vol *= ext[a];
+    }
+    if (!(vol > 0.0) || !(reach_xy > 0.0) || !std::isfinite(vol))
+        return 1;
+    const double rho1 = n1 / vol, rho2 = n2 / vol;
+    int best = 1;
+    double least = 0.0;
+    for (int k = 1; k <= PC_MAX_XYK; k++) {
+        for (int a = 0; a < 2; a++)
+            if (std::floor(ext[a] / (reach_xy / k)) < 2 * k + 1)
+                return best;   // (too few columns to refine)
+        pc_grid g;
+        if (plan_grid_k(lo, hi, boxsize, reach_xy, reach_z, slices_per_reach, &g, k, zball))
+            return best;
+        const double w[2] = {g.width[0], g.width[1]};
+        const double area = w[0] * w[1];
+        const double b = std::min(PC_BLOCK_I / (rho1 * area), ext[2]);
+        // slices further apart than asked widen every window by theirs
+        const double asked = reach_z / slices_per_reach;
+        const double coarse = g.width[2] > 1.5 * asked ? 2.0 * (g.width[2] - asked) : 0.0;
+        double cost = 6000.0 * (k - 1);
+        for (int ox = -k; ox <= k; ox++)
+            for (int oy = -k; oy <= k; oy++) {
+                const double dx = std::max(std::abs(ox) - 1, 0) * w[0];
+                const double dy = std::max(std::abs(oy) - 1, 0) * w[1];
+                const double d2 = dx * dx + dy * dy;
+                if (d2 >= reach_xy * reach_xy)
+                    continue;
+                const double z = zball ? std::sqrt(reach_xy * reach_xy - d2) : reach_z;
+                const double run = rho2 * area * std::min(2.0 * z + b + coarse, ext[2]);
+                cost += PC_BLOCK_I * run + item_cost;
+            }
+        if (k == 1 && cost * n1 / PC_BLOCK_I * (autocorr ? 0.5 : 1.0) < 2e8)
+            return 1;
+        // (a few percent: the estimate's own worth)
+        if (k == 1 || cost < 0.97 * least) {
+            least = cost;
+            best = k;
+        }
+    }
+    return best;
 }
 
 // Angular grid of section "Partitioning the particles on a grid: angular
@@ -901,6 +912,20 @@ extern "C" cf_status cf_plan_grid_ex(const double lo[3], const double hi[3], dou
 }
 
 static_assert(sizeof(cf_sky_band) == sizeof(pc_band), "cf_sky_band mirrors pc_band");
+
+extern "C" cf_status cf_plan_refine(const double lo[3], const double hi[3], double boxsize,
+                                    double reach_xy, double reach_z, int32_t slices_per_reach,
+                                    int32_t ball, double n1, double n2, int32_t autocorr,
+                                    double item_cost, int32_t *k)
+{
+    double zl[3] = {0, 0, 0}, zh[3] = {0, 0, 0};
+    if (!k || std::isnan(boxsize) || (boxsize <= 0.0 && (!lo || !hi)) ||
+        slices_per_reach < 1 || !(n1 >= 0.0) || !(n2 >= 0.0) || !(item_cost >= 0.0))
+        return CF_EINVAL;
+    *k = pc::choose_refine(lo ? lo : zl, hi ? hi : zh, boxsize, reach_xy, reach_z, ball != 0,
+                           slices_per_reach, n1, n2, autocorr != 0, item_cost);
+    return CF_OK;
+}
 
 extern "C" cf_status cf_plan_sky_grid(double chord_reach, double zlo, double zhi,
                                       int32_t slices, int32_t ra_refine, cf_sky_plan *out,

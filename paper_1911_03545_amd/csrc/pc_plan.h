@@ -24,8 +24,8 @@ int plan_grid(const double lo[3], const double hi[3], double boxsize, double rea
 // two sides spread evenly over the domain); item_cost: pairs that a work item
 // costs beyond its own
 int choose_refine(const double lo[3], const double hi[3], double boxsize, double reach_xy,
-                  double reach_z, bool zball, double n1, double n2, bool autocorr,
-                  double item_cost);
+                  double reach_z, bool zball, int slices_per_reach, double n1, double n2,
+                  bool autocorr, double item_cost);
 // angular grid of unit vectors (overrides n, ncell, zreach and the slice
 // fields of a grid planned on the vectors' bounding box)
 int plan_sky_grid(double chord_reach, double zlo, double zhi, int slices, int ra_refine,
