@@ -703,14 +703,15 @@ cf_status grid_side(cf_ctx *c, const SideData &s, const pc_cat *cats_dev, bool w
         (st = ensure(c, B_PERM, sizeof(int32_t) * (size_t)n)) ||
         (st = ensure(c, B_REC, 32 * (size_t)n)) ||
         (st = ensure(c, B_SCANTMP, sizeof(int32_t) * pc::scan_tmp_elems(ncells))) ||
-        (st = ensure(c, X, sizeof(float) * (size_t)n)) ||
-        (st = ensure(c, Y, sizeof(float) * (size_t)n)) ||
-        (st = ensure(c, Z, sizeof(float) * (size_t)n)) ||
         (st = ensure(c, XD, sizeof(double) * (size_t)n)) ||
         (st = ensure(c, YD, sizeof(double) * (size_t)n)) ||
         (st = ensure(c, ZD, sizeof(double) * (size_t)n)) ||
         (st = ensure(c, CS, sizeof(int32_t) * (size_t)n)))
         return st;
+    if (!g.no_f32)
+        for (BufId b : {X, Y, Z})
+            if ((st = ensure(c, b, sizeof(float) * (size_t)n)))
+                return st;
     if (weighted && (st = ensure(c, WD, sizeof(double) * (size_t)n)))
         return st;
     if (Q != B_COUNT && (st = ensure(c, Q, 4 * sizeof(float) * (size_t)n)))
@@ -1271,11 +1272,10 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     // ---- grid ------------------------------------------------------------
     // (|b|^2 for the expanded forms: on the j side only)
     if (d64 > 0.0) {
-        const BufId q = autocorr ? B_Q1 : B_Q2;
-        if ((st2 = ensure(c, q, sizeof(double) * (size_t)n2)) ||
-            (!autocorr && (st2 = ensure(c, B_Q1, sizeof(double) * (size_t)n1))))
+        if ((st2 = ensure(c, autocorr ? B_Q1 : B_Q2, sizeof(double) * (size_t)n2)))
             return st2;
-        g.q64 = dptr<double>(c, B_Q1);
+        g.no_f32 = 1;
+        g.q64 = autocorr ? dptr<double>(c, B_Q1) : nullptr;
     }
     if ((st2 = grid_side(c, s1, cats1_dev, weighted, g, B_START1, B_X1, B_Y1, B_Z1, B_XD1, B_YD1,
                          B_ZD1, B_WD1, B_CS1, (xy_mag > 0.0 && autocorr) ? B_Q1 : B_COUNT,

@@ -110,8 +110,10 @@ struct pc_grid {
     double dec_lo;
     double inv_hs;
     double sky_reach;   // angular reach with its margins (radians)
-    // expanded binary64 r sweep: receives c^2 |b|^2 of every sorted point (or
-    // NULL), c = fscale; the float32 coordinates are then not written
+    // expanded binary64 r sweep: no_f32 says that the float32 coordinates are not
+    // written, and q64 (its j side) receives c^2 |b|^2 of every sorted point, c =
+    // fscale
+    int32_t no_f32;
     double *q64;
     const pc_band *bands;
 };

@@ -585,8 +585,9 @@ __device__ __forceinline__ void store_sorted(const pc_grid &g, const double4 &r,
     zd[d] = r.z;
     if (wd)
         wd[d] = r.w;
-    if (g.q64) {
-        g.q64[d] = ((r.x * r.x + r.y * r.y) + r.z * r.z) * (g.fscale * g.fscale);
+    if (g.no_f32) {
+        if (g.q64)
+            g.q64[d] = ((r.x * r.x + r.y * r.y) + r.z * r.z) * (g.fscale * g.fscale);
         return;
     }
     float fx, fy, fz;
