@@ -995,6 +995,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     const bool keep_uploads = !ctl.capture && !c->arena;
     const size_t cats1_bytes = sizeof(pc_cat) * (size_t)ncat;
     pc_cat *put1 = nullptr;
+    bool fresh_cats1 = true;
     if (!(keep_uploads &&
           upload_fresh(c->up_cats1, c->buf[B_CATS1].p, s1.cats.data(), cats1_bytes))) {
         if (ncat == 1) {
@@ -1004,15 +1005,15 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
             HIPCHK(hipMemcpyAsync(c->buf[B_CATS1].p, pin + p_cats1, cats1_bytes,
                                   hipMemcpyHostToDevice, c->stream));
         }
-        if (keep_uploads)
-            upload_keep(c->up_cats1, c->buf[B_CATS1].p, s1.cats.data(), cats1_bytes);
-        else
-            c->up_cats1 = cf_ctx::Upload{};
+        c->up_cats1 = cf_ctx::Upload{};   // (kept once its upload is queued)
+        fresh_cats1 = false;
     }
     if (put1 || !autocorr)
         HIPCHK(pc::launch_put_cats(c->stream, s1.cats.data(), put1,
                                    autocorr ? nullptr : s2.cats.data(),
                                    autocorr ? nullptr : dptr<pc_cat>(c, B_CATS2)));
+    if (keep_uploads && !fresh_cats1)
+        upload_keep(c->up_cats1, c->buf[B_CATS1].p, s1.cats.data(), cats1_bytes);
     const pc_cat *cats1_dev = dptr<pc_cat>(c, B_CATS1);
     const pc_cat *cats2_dev = autocorr ? cats1_dev : dptr<pc_cat>(c, B_CATS2);
 
