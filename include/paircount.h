@@ -122,8 +122,9 @@ typedef struct cf_options {
                                    graph (periodic, device-resident inputs)    */
     int32_t autotune;           /* time slices_per_reach and chunk candidates
                                    (and, when left at 0, angular_grid 8 / 32
-                                   for angular counts or xy_refine 2 for 3-D
-                                   grids) on the first call of a workload class
+                                   for angular counts or, for 3-D grids, the
+                                   refinements beside the one that 0 takes)
+                                   on the first call of a workload class
                                    and reuse the fastest (cached per context)  */
     int32_t weight_type;        /* cf_weight: weight of a pair from the weights
                                    of its two points (needs weights unless

@@ -959,7 +959,7 @@ __device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b
 // us for 10^6 points): it counts the items of its segments, the workgroup sums
 // them, and the items go to
 //   MODE 0: nowhere; the workgroup's total to wcnt (ordered lists, first pass)
-//   MODE 1: the places after the scanned totals woff (second pass; the last
+//   MODE 1: the places after the scanned totals woff (second pass; the first
 //           workgroup leaves the list's length in n_items)
 //   MODE 2: places taken from n_items with one atomic per workgroup.
 // (The caller's comment says which list pays where.)

@@ -40,8 +40,8 @@ struct SweepArgs {
     const pc_wfixed *wfx;
     unsigned long long *g_wfix;
     // sets of global bins (power of two; 1 for batches): workgroup b merges into
-    // set b mod hsets.  1024 workgroups adding to the same 20 bins queue at a
-    // handful of addresses for longer than a small call's pairs take.
+    // set b mod hsets.  Several where pairs have weights: the binary64 sums of all
+    // workgroups queue at the same few addresses (counts alone gained nothing).
     int32_t hsets;
     double *g_rhist;       // sums of separation x pair weight (mean separation), or NULL
     int32_t ravg;          // 0: no mean separation; 1: distance sqrt(s);

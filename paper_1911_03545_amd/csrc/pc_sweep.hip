@@ -1704,10 +1704,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             }
         }
     }
-    // the result of a take still in flight (past the last item) is waited
-    // for, not left outstanding (a counter value is never negative)
-    if (AHEAD && pend && __builtin_amdgcn_readfirstlane(pv) < 0)
-        rechecks++;
     if (PRIV) {
         flush_hist<UNC>(a, L, lane, PC_WAVE, W, cur_cat);
     } else {
