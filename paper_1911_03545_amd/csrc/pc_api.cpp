@@ -1065,10 +1065,12 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
                             : pc::choose_refine(lo, hi, boxsize, reach_xy, reach_z,
                                                 metric != PC_METRIC_RPPI, opt.slices_per_reach,
                                                 (double)n1, (double)n2, autocorr,
-                                                (sky || metric == PC_METRIC_RPPI ? 2000.0
-                                                 : weighted                      ? 4300.0
-                                                                                 : 2500.0) *
-                                                    (prec == CF_PREC_FP64 || sky ? 0.5 : 1.0));
+                                                sky || metric == PC_METRIC_RPPI
+                                                    ? (prec == CF_PREC_FP64 || sky ? 1000.0
+                                                                                   : 2000.0)
+                                                : prec == CF_PREC_FP64 ? 1250.0
+                                                : weighted             ? 4300.0
+                                                                       : 2500.0);
     pc_grid g;
     // r, angular chords and on-sky pairs are bounded by a 3-D ball
     int rc = pc::plan_grid(lo, hi, boxsize, reach_xy, reach_z, opt.slices_per_reach, &g,

@@ -181,17 +181,18 @@ int plan_grid_k(const double lo_in[3], const double hi_in[3], double boxsize,
 // grows longer and its items more and shorter.  Measured at k = 1 and 2 (sweep
 // of 10^6 points at density 0.0135, reach 25): DD(r) 623 and 626 us, DD(rp, pi)
 // 1377 and 1248; 4*10^6 weighted points (density 0.003, reach 50) 6.80 and 6.06
-// ms; solved for the cost of an item: 2000 (rp, pi) to 4300 (weighted) pairs,
-// half of that where pairs are formed in binary64 (DD(r) 958 and 833 us, on-sky
-// 8.7 and 6.0 ms).
+// ms; solved for the cost of an item: 2000 pairs for (rp, pi), 2500 for DD(r) and
+// 4300 for weighted DD(r); where pairs are formed in binary64, 1000 and 1250 (DD(r)
+// 958 and 833 us, on-sky 8.7 and 6.0 ms), with weights too: 10^6 points, reach 25,
+// calls of 1.51 and 1.37 ms, with fixed-point sums 2.59 and 2.40, mean separations
+// 2.41 and 2.24; 2*10^6, reach 20: 2.99 and 2.89, 4.90 and 4.55, 4.74 and 4.45.
 // Each further k adds about 16 us of gridding and listing at 10^6 points (6000
 // pairs a block).  Short lists (below 2*10^8 pairs) wait for latency, not work.
-// Over 74 workloads (5*10^4 to 4*10^7 points, reach a fifth to a fiftieth of the
+// Over 110 workloads (5*10^4 to 4*10^7 points, reach a fifth to a fiftieth of the
 // box, DD(r), (rp, pi), on-sky, weighted, mean separations, cross, both
 // precisions) the choice was at most 3.5% slower than k = 1 (2*10^5 points at
 // density 0.0128, reach 25: 256 and 248 us), 4 to 30% faster wherever it was not
-// 1, and within 5% of the best k but for weighted binary64 DD(r) (1.56 ms, 1.37
-// at 2) and on-sky pairs (2.96, 2.67 at 3).
+// 1, and within 6% of the best k but for on-sky pairs (2.96 ms, 2.67 at 3).
 // The grids priced are those that plan_grid builds: columns no narrower than
 // its 1024 an axis allow, and slices as far apart as its cells allow.
 int choose_refine(const double lo[3], const double hi[3], double boxsize, double reach_xy,
