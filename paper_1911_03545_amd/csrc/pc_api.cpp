@@ -46,8 +46,8 @@ enum BufId {
 enum {
     M_FLAGS = 0,        // unsigned
     M_RQCOUNT = 16,     // unsigned
-    M_CAND = 32,        // u64
-    M_SIZES = 40,       // 2 int32: work items, blocks
+    M_CAND = 32,        // u64 (in the host copy only)
+    M_SIZES = 40,       // 2 int32: work items, blocks (blocks in the host copy only)
     M_FLUSH = 48,       // unsigned: mid-sweep histogram flushes
     M_COUNTED = 52,     // int32: work items counted ahead of the list (first calls)
     M_OUT6 = 64,        // 6 doubles (in the host copy only)
@@ -1337,9 +1337,8 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     const int32_t *start1 = dptr<int32_t>(c, B_START1);
     const int32_t *start2 = autocorr ? start1 : dptr<int32_t>(c, B_START2);
     const pc_block *blocks = dptr<pc_block>(c, B_BLOCKS);
-    unsigned long long *cand = (unsigned long long *)(misc(c) + M_CAND);
     int32_t *items_dev = (int32_t *)(misc(c) + M_SIZES);
-    int32_t *nblk_dev = items_dev + 1;
+    int32_t *tallies = dptr<int32_t>(c, B_CTRS);   // candidates and blocks
     // one pass of the work list kernel (see pc_launch.h)
     auto list_pass = [&](int mode, pc_item *items, int32_t cap, unsigned *fl, int32_t *count) {
         return pc::launch_items(c->stream, mode, (int32_t)nblocks, blocks, g, start2,
@@ -1347,7 +1346,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
                                 dptr<int32_t>(c, B_ICNT), dptr<int32_t>(c, B_IOFF), items, cap,
                                 fl, dptr<int32_t>(c, autocorr ? B_CS1 : B_CS2),
                                 (items && g.xy_local) ? dptr<int32_t>(c, B_ICELL) : nullptr,
-                                count, cand, nblk_dev);
+                                count, tallies);
     };
     if (ordered) {
         HIPCHK(list_pass(0, nullptr, 0, nullptr, nullptr));
@@ -1389,7 +1388,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
                                    : (int32_t *)(misc(c) + M_COUNTED),
                               sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         if (!ordered)
-            HIPCHK(pc::launch_zero(c->stream, misc(c) + M_CAND, M_SIZES + 8 - M_CAND));
+            HIPCHK(pc::launch_zero(c->stream, tallies, PC_STREAM_BYTES));
         HIPCHK(hipStreamSynchronize(c->stream));
         memcpy(&hcounts[0], pin + p_misc, 4);
         n_items = hcounts[0];
@@ -1625,7 +1624,7 @@ cf_status run(cf_ctx *c, RunCtl &ctl, int metric, bool theta, const cf_catalog *
     HIPCHK(pc::launch_finalize(c->stream, ncat, (int32_t)nbt, autocorr ? 1 : 0, hb.hdr.e0_zero,
                                cats1_dev, a.g_hist, a.g_whist, a.g_rhist, wsq, a.g_wfix,
                                wsq_fix, wfx, outc, outw, outr, hsets, misc(c), pin + p_misc,
-                               M_SIZE));
+                               M_SIZE, tallies, M_CAND, M_SIZES + sizeof(int32_t)));
     record(c, timing, 6);
     if (ctl.capture)
         return CF_OK;

@@ -23,8 +23,11 @@
 #define PC_STREAMS 64
 #define PC_STREAM_STRIDE 64
 // (each stream's ints hold its counter and, half way, a copy of the 64-bit mask
-// of exhausted streams)
+// of exhausted streams; before the sweep the work list adds its candidate pairs,
+// 64 bits, and blocks to two more of them, a share to each stream)
 #define PC_STREAM_BYTES (4 * PC_STREAMS * PC_STREAM_STRIDE)
+#define PC_STREAM_CAND 8
+#define PC_STREAM_BLOCKS 16
 #define PC_MAX_EDGES 1025      // r / rp / theta edges
 #define PC_MAX_NPI 1024
 #define PC_MAX_BINS_TOTAL 4096 // r bins, or nrp * npi

@@ -965,13 +965,15 @@ __device__ __forceinline__ void grid_segments(const SegCtx &c, const pc_block &b
 // (The caller's comment says which list pays where.)
 // Items beyond `cap` are not written; the flag PC_FLAG_ITEMS reports them (a
 // repeated call whose inputs now need more items than it was built for).
-// cand and n_blocks (modes 0 and 2): candidate pairs and blocks.
+// tallies (modes 0 and 2): candidate pairs and blocks, spread over the streams'
+// lines: on one address each the adds of 90 000 workgroups queued (256 batched
+// catalogues: counting pass 7.3 ms, now 1.6).
 constexpr int kItemThreads = 256;
 template <bool SKY, int MODE>
 __global__ __launch_bounds__(kItemThreads) void k_items(
     int32_t nblocks, int32_t visits, const pc_block *blocks, SegCtx c, int chunk, int32_t *wcnt,
     const int32_t *woff, pc_item *items, int32_t cap, unsigned *flags, const int32_t *cs2,
-    int32_t *icell, int32_t *n_items, unsigned long long *cand, int32_t *n_blocks)
+    int32_t *icell, int32_t *n_items, int32_t *tallies)
 {
     const unsigned long long t0 = (unsigned long long)blockIdx.x * kItemThreads;
     const unsigned gv = 8u * (unsigned)visits;
@@ -1024,10 +1026,11 @@ __global__ __launch_bounds__(kItemThreads) void k_items(
                 my += s_cand[w];
                 nb += s_blk[w];
             }
+            int32_t *t = tallies + (blockIdx.x % PC_STREAMS) * PC_STREAM_STRIDE;
             if (my)
-                atomicAdd(cand, my);
+                atomicAdd(reinterpret_cast<unsigned long long *>(t + PC_STREAM_CAND), my);
             if (nb)
-                atomicAdd(n_blocks, nb);
+                atomicAdd(t + PC_STREAM_BLOCKS, nb);
             if (MODE == 0)
                 wcnt[wg] = sum;
             else
@@ -1343,7 +1346,7 @@ hipError_t launch_items(hipStream_t s, int mode, int32_t nblocks, const pc_block
                         int autocorr, int chunk, int32_t *wcnt, const int32_t *woff,
                         pc_item *items, int32_t cap, unsigned *flags,
                         const int32_t *cell2_sorted, int32_t *icell, int32_t *n_items,
-                        unsigned long long *cand, int32_t *n_blocks)
+                        int32_t *tallies)
 {
     SegCtx c{g, start2, cell1_sorted, autocorr};
     const bool sky = g.nband > 0;
@@ -1354,7 +1357,7 @@ hipError_t launch_items(hipStream_t s, int mode, int32_t nblocks, const pc_block
     hipLaunchKernelGGL(fn,
                        dim3((unsigned)item_workgroups(nblocks, g, autocorr)),
                        dim3(kItemThreads), 0, s, nblocks, visits, blocks, c, chunk, wcnt, woff, items, cap,
-                       flags, cell2_sorted, icell, n_items, cand, n_blocks);
+                       flags, cell2_sorted, icell, n_items, tallies);
     return hipGetLastError();
 }
 

@@ -167,18 +167,19 @@ hipError_t launch_block_emit(hipStream_t s, int32_t ncol, int32_t nz, const int3
 // (item_workgroups of them); mode 1: items to the places after woff, the scan
 // of those counts, and the list's length to n_items; mode 2: items to places
 // taken from n_items (zeroed first) in one pass.  At most `cap` items are
-// written (PC_FLAG_ITEMS in flags, unless NULL, when there are more).  cand and
-// n_blocks (zeroed first; modes 0 and 2) receive the candidate pairs and the
-// blocks.  icell (optional, with cell2_sorted): the cell id of every item's
-// first j point, beside the items (the float32 sweep of 3-D grids reads it one
-// item ahead, with the item, to place its lanes in the j column's frame).
+// written (PC_FLAG_ITEMS in flags, unless NULL, when there are more).  tallies
+// (the streams' lines, zeroed first; modes 0 and 2) receives the candidate pairs
+// and the blocks, a share to each stream (PC_STREAM_CAND, PC_STREAM_BLOCKS).
+// icell (optional, with cell2_sorted): the cell id of every item's first j point,
+// beside the items (the float32 sweep of 3-D grids reads it one item ahead, with
+// the item, to place its lanes in the j column's frame).
 int64_t item_workgroups(int64_t nblocks, const pc_grid &g, int autocorr);
 hipError_t launch_items(hipStream_t s, int mode, int32_t nblocks, const pc_block *blocks,
                         const pc_grid &g, const int32_t *start2, const int32_t *cell1_sorted,
                         int autocorr, int chunk, int32_t *wcnt, const int32_t *woff,
                         pc_item *items, int32_t cap, unsigned *flags,
                         const int32_t *cell2_sorted, int32_t *icell, int32_t *n_items,
-                        unsigned long long *cand, int32_t *n_blocks);
+                        int32_t *tallies);
 // wmode: 0 unweighted, 1 weight sums, 2 weight and mean-separation sums
 hipError_t launch_sweep(hipStream_t s, int metric, bool fp32, int wmode, const SweepArgs &a,
                         int nwg);
@@ -199,7 +200,8 @@ hipError_t launch_wsq_fixed(hipStream_t s, int32_t ncat, int64_t ncell, const in
                             unsigned long long *out);
 // counts (and weight sums, mean separations) of every catalogue: doubling
 // and self-pairs of autocorrelations; the mean separation is the separation
-// sum over the weight sum
+// sum over the weight sum.  misc_bytes of misc go to misc_out, the sums of the
+// tallies to its bytes cand_at (64 bits) and blocks_at
 hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
                            const pc_cat *cats, const unsigned long long *g_hist,
                            const double *g_whist, const double *g_rhist, const double *wsq,
@@ -207,7 +209,8 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
                            double *out_ravg, int32_t hsets, const void *misc, void *misc_out,
-                           size_t misc_bytes);
+                           size_t misc_bytes, const int32_t *tallies, size_t cand_at,
+                           size_t blocks_at);
 // resident sweep workgroups per CU for a dynamic LDS size
 // waves per sweep workgroup
 int sweep_waves();

@@ -1915,12 +1915,31 @@ __global__ void k_finalize(int32_t ncat, int32_t nbt, int autocorr, int e0_zero,
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum, double *out_ravg,
                            int32_t hsets, const unsigned *misc, unsigned *misc_out,
-                           int32_t misc_words)
+                           int32_t misc_words, const int32_t *tallies, int32_t cand_word,
+                           int32_t blocks_word)
 {
     // (every kernel that writes the flags and counters ran before this one)
-    if (blockIdx.x == 0)
+    if (blockIdx.x == 0) {
         for (int k = threadIdx.x; k < misc_words; k += blockDim.x)
-            misc_out[k] = misc[k];
+            if (k != cand_word && k != cand_word + 1 && k != blocks_word)
+                misc_out[k] = misc[k];
+        if (threadIdx.x < PC_WAVE) {
+            // one stream per lane
+            const int32_t *t = tallies + threadIdx.x * PC_STREAM_STRIDE;
+            unsigned long long cand =
+                *reinterpret_cast<const unsigned long long *>(t + PC_STREAM_CAND);
+            int32_t nb = t[PC_STREAM_BLOCKS];
+            for (int off = PC_WAVE / 2; off > 0; off >>= 1) {
+                cand += __shfl_xor(cand, off);
+                nb += __shfl_xor(nb, off);
+            }
+            if (threadIdx.x == 0) {
+                misc_out[cand_word] = (unsigned)cand;
+                misc_out[cand_word + 1] = (unsigned)(cand >> 32);
+                misc_out[blocks_word] = (unsigned)nb;
+            }
+        }
+    }
     const int64_t total = (int64_t)ncat * nbt;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
          t += (int64_t)gridDim.x * blockDim.x) {
@@ -2084,7 +2103,8 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                            const unsigned long long *wsq_fix, const pc_wfixed *wfx,
                            unsigned long long *out_counts, double *out_wsum,
                            double *out_ravg, int32_t hsets, const void *misc, void *misc_out,
-                           size_t misc_bytes)
+                           size_t misc_bytes, const int32_t *tallies, size_t cand_at,
+                           size_t blocks_at)
 {
     const int64_t total = (int64_t)ncat * nbt;
     int64_t g = (total + 255) / 256;
@@ -2093,7 +2113,9 @@ hipError_t launch_finalize(hipStream_t s, int32_t ncat, int32_t nbt, int autocor
                        e0_zero, cats, g_hist, g_whist, g_rhist, wsq, g_wfix, wsq_fix, wfx,
                        out_counts, out_wsum, out_ravg, hsets,
                        static_cast<const unsigned *>(misc), static_cast<unsigned *>(misc_out),
-                       (int32_t)(misc_bytes / sizeof(unsigned)));
+                       (int32_t)(misc_bytes / sizeof(unsigned)), tallies,
+                       (int32_t)(cand_at / sizeof(unsigned)),
+                       (int32_t)(blocks_at / sizeof(unsigned)));
     return hipGetLastError();
 }
 
